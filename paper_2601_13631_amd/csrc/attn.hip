@@ -7,14 +7,16 @@
 // Rows of one KV head are r = t*G + i (query t, head g*G + i), so the G query
 // heads that share a KV head share every K/V tile.  A workgroup owns 128 rows
 // (4 waves x 32) and one contiguous slice ("split") of the key positions.  At
-// its start it resolves every key of its slice to a source code (a prefix row
-// of the K/V source, a suffix token, or no key) in LDS, so the tile loads are
-// branch-free.  Per 64-key stage:
+// its start it resolves the slice in units of min(c, 32) keys to source rows
+// (the prefix K/V source or the suffix) in LDS.  Per 64-key stage, in two halves
+// of 32 keys:
 //   S^T = K Q^T   bf16 MFMA 32x32x16, A = K rows from LDS, B = Q^T in
 //                 registers: every lane owns one query row and 16 keys;
-//   online softmax in fp32 (exp2 with sm_scale*log2 e folded in) with a lazy
-//                 reference: it moves only when a stage's maximum exceeds it
-//                 by more than 2^8, so most stages skip the O rescale;
+//   numerators    exp2 in fp32 (sm_scale*log2 e folded in) against a fixed
+//                 reference per row: the maximum over the slice's first 32
+//                 keys.  A slice whose sums or outputs then leave a guard (or
+//                 that had no reference) is done again against its own maximum,
+//                 so the result never depends on the guess;
 //   O^T += V^T P^T  A = V^T read from LDS with the transposing
 //                 ds_read_b64_tr_b16, B = P^T straight from the softmax
 //                 registers.
@@ -24,8 +26,26 @@
 // Splits write their normalised partial output O/l in bf16 (the output's own
 // type and range) plus (reference, l) in fp32; a combine kernel merges them in
 // split order (deterministic).
+//
+// What bounds it: the matrix cores (32 MFMAs of 32 cycles per wave and stage at
+// D = 128), the numerators' VALU work (112 instructions, the exponentials 8.6
+// cycles each) and the LDS reads (32 KB per wave and stage, 128 bytes a cycle
+// per CU) would each take about half of a stage's time, so they have to run side
+// by side.  Hence the runs of the stage loop below, K/V rows that go straight
+// from memory to LDS, and no running maximum (a chain from the MFMAs through the
+// maximum to the exponentials).  Measured against a loop with the running
+// maximum, register staging and operands read right before their MFMA, at 1.85
+// GHz (what the chip holds under this load): 32K layer 27 -> 24 us, 64K layer
+// 154 -> 119 us, 128K layer 367 -> 286 us, 8,000 of 16,000 tokens with 512
+// queries and 32 heads 107 -> 72 us (949 TFLOP/s).  Not faster: 64 rows per wave
+// (half the LDS reads, one wave per SIMD: 3,350 cycles per stage and 64 rows,
+// two waves of 32 rows 3,440), and a loop that spreads the numerators over all
+// 32 MFMAs by running a product of the next stage early (128K 295 against 302 us
+// of the loop below, small grids 10% slower for its longer prologue).
 
 #include <atomic>
+#include <type_traits>
+#include <utility>
 
 #include "ckv_internal.h"
 
@@ -39,16 +59,14 @@ constexpr int kWaveRows = 32;
 constexpr int kBlockRows = kWaves * kWaveRows;  // 128
 constexpr int kTile = 64;                       // keys per LDS stage
 constexpr int kSub = 32;                        // keys per MFMA product
-constexpr int kMaxSliceKeys = 1024;             // keys per workgroup slice (8 KiB of key tables)
-constexpr float kLazy = 8.f;                    // headroom of the lazy softmax reference (log2 units)
-// Key tables: for every key of a slice, the row of its K/V source (as a byte
-// offset from the source's base when all of them fit in 32 bits) and its
-// visibility threshold -- a query t sees the key iff t >= thr.  thr = -1 marks
-// a row of the prefix source (seen by every query); a suffix token p has
-// thr = p (causal) and a row of the suffix source; a padding key has
-// thr = kNever and suffix row 0 (always present; its weight is forced to 0).
-constexpr int kPrefix = -1;
-constexpr int kNever = 0x7fffffff;
+constexpr float kGuard = 0x1p64f;               // a sum of numerators above this is taken again
+// Unit tables: a slice's keys in units of min(c, 32) keys, each inside one chunk
+// or inside the suffix (kc is a multiple of c).  base: the unit's first row in
+// its source (a byte offset when every row of both sources lies below 4 GiB);
+// valid: how many of its rows exist (fewer at the end of a short last chunk
+// and of the suffix, none for an index that names no chunk).
+constexpr int kMaxSliceUnits = 1536;  // 12 KiB of tables: two workgroups still share a CU's LDS
+constexpr int kMaxSliceStages = 512;
 
 // MFMA row p of the K operand holds key kappa(p); afterwards register v of a
 // lane in half h holds key 16*(v/8) + 8*h + v%8.
@@ -57,16 +75,17 @@ __device__ __forceinline__ int kappa(int p) {
   return 16 * (i >> 1) + 8 * h + 4 * (i & 1) + j;
 }
 
-// K stage: rows padded by one 16-byte segment, so the operand reads (16
-// consecutive lanes = 16 distinct rows, same segment) start 4 banks apart and
-// every fragment is an immediate offset from one per-lane base.
+// LDS stages hold kTile rows of D bf16, unpadded (the direct-to-LDS loads write
+// lane i's 16 bytes at base + 16 i), with the 16-byte segments of a row
+// permuted by an XOR that depends on the row: segment s of row r sits at
+// position s ^ swz(r).  K: any 16 consecutive MFMA rows (kappa) then read one
+// segment column from all 64 banks.
 template <int D>
-struct KLds {
-  static constexpr int kRow = D + 8;
-};
+__device__ __forceinline__ int k_swz(int row) {
+  return D == 128 ? (row & 15) : ((row >> 1) & 7);
+}
 
-// V stage: XOR swizzle of 16-byte segments, conflict-free for the transposing
-// reads.
+// V: conflict-free for the transposing reads.
 template <int D>
 __device__ __forceinline__ int v_swz(int row) {
   if constexpr (D == 128)
@@ -95,6 +114,7 @@ struct AttnArgs {
   int64_t n, m;
   int c;
   int log2c;               // log2(c) when c is a power of two, else -1
+  int log2u;               // log2 of the keys per unit: min(c, 32)
   const uint16_t* ks;      // [S][Hkv][D]
   const uint16_t* vs;
   uint16_t* out;           // [S][Hq][D]
@@ -115,17 +135,17 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t raw_rsrc(const void* p, uint32
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, (int)bytes, 0x00020000);
 }
 
-// Table entries of compact key position pos, in two steps so that a workgroup
-// can issue all its index loads before using any: key_chunk_loads fetches
-// sel[u] (and the slot table entry) of the key's chunk u, key_entry finishes.
-// Row off of kept chunk u sits at source row slot*rows_per_slot + off, slot =
-// chunk_off[u] (slot table), sel[u] (spans read in place) or u (compact
-// copy).
+// Chunk of compact prefix position pos.
 __device__ __forceinline__ int chunk_of(const AttnArgs& a, int pos) {
   return a.log2c >= 0 ? (pos >> a.log2c) : (int)((uint32_t)pos / (uint32_t)a.c);
 }
 
-__device__ __forceinline__ void key_chunk_loads(const AttnArgs& a, int pos, int& j, int& slot) {
+// The unit that starts at compact position pos, in two steps so that a thread
+// can issue its index loads before using any: unit_chunk fetches sel[u] (and the
+// slot table entry) of its chunk u, unit_entry finishes.  Kept chunk u begins at
+// source row slot*rows_per_slot, slot = chunk_off[u] (slot table), sel[u]
+// (spans read in place) or u (compact copy).
+__device__ __forceinline__ void unit_chunk(const AttnArgs& a, int pos, int& j, int& slot) {
   j = 0;
   slot = 0;
   if (pos < a.kc) {
@@ -135,234 +155,238 @@ __device__ __forceinline__ void key_chunk_loads(const AttnArgs& a, int pos, int&
   }
 }
 
-__device__ __forceinline__ void key_entry(const AttnArgs& a, int pos, int j, int slot_tab, int& row,
-                                          int& thr) {
+__device__ __forceinline__ void unit_entry(const AttnArgs& a, int pos, int j, int slot_tab, int& row,
+                                           int& valid) {
+  const int size = 1 << a.log2u;
   row = 0;
-  thr = kNever;
+  valid = 0;
   if (pos < a.kc) {
     const int u = chunk_of(a, pos);
     const int off = pos - u * a.c;
     if (j < 0 || (int64_t)j >= a.m) return;
-    if ((int64_t)j * a.c + off >= a.n) return;  // past n in a short last chunk
+    const int64_t left = a.n - ((int64_t)j * a.c + off);  // <= 0: past n in a short last chunk
+    if (left <= 0) return;
+    valid = (int)min<int64_t>(left, size);
     const int slot = a.chunk_off ? slot_tab : (a.direct ? j : u);
     row = slot * a.rows_per_slot + off;
-    thr = kPrefix;
-  } else if (pos < a.kc + a.S) {
+  } else if (a.with_suffix && pos - a.kc < a.S) {
     row = pos - a.kc;
-    thr = row;
+    valid = min(a.S - row, size);
   }
 }
 
-// The K/V rows of one 64-key stage, fetched into registers (while the previous
-// stage is consumed from LDS) and then written to the other LDS buffer.  Each
-// thread moves kPer 16-byte pieces of K and of V: piece p is segment tid %
-// kSegs of key tid / kSegs + p * kKeyStep.
+// Flags of a stage: bit 0, some row of the block must not see some of its keys;
+// bits 1-2, its keys are 64 rows of the prefix source, 64 rows of the suffix
+// source, or anything else.
+constexpr int kStageMask = 1, kStagePrefix = 1 << 1, kStageSuffix = 2 << 1, kStageMixed = 3 << 1;
+
+// The direct-to-LDS loads of one 64-key stage: instruction p of wave w moves
+// the K (or V) rows of keys p*kKeyStep + w*kRowsPerLoad .. +kRowsPerLoad-1,
+// kSegs lanes per row.
 template <int D>
-struct TileRegs {
+struct Stage {
   static constexpr int kSegs = D / 8;
-  static constexpr int kPer = kTile * kSegs / (kWaves * 64);  // 16-byte pieces per thread
-  static constexpr int kKeyStep = kWaves * 64 / kSegs;
-  u32x4 k[kPer], v[kPer];
+  static constexpr int kRowsPerLoad = 64 / kSegs;
+  static constexpr int kKeyStep = kWaves * kRowsPerLoad;
+  static constexpr int kPer = kTile / kKeyStep;
 };
 
-// The table entries of this thread's keys of one stage (read one stage ahead,
-// so the row loads never wait on LDS): the row's byte offset from its source's
-// base (AttnArgs::off32) or the row itself, and the threshold.
-template <int D>
-struct TileKeys {
-  int row[TileRegs<D>::kPer], thr[TileRegs<D>::kPer];
-};
+using LdsPtr = __attribute__((address_space(3))) void*;
 
-template <int D>
-__device__ __forceinline__ void tile_keys(const int* rows, const int* thrs, TileKeys<D>& tk) {
-  const int key0 = threadIdx.x / TileRegs<D>::kSegs;
-#pragma unroll
-  for (int p = 0; p < TileRegs<D>::kPer; ++p) {
-    tk.row[p] = rows[key0 + p * TileRegs<D>::kKeyStep];
-    tk.thr[p] = thrs[key0 + p * TileRegs<D>::kKeyStep];
-  }
+// 16 bytes per lane from memory to lds + 16 * lane (lds is uniform).  Buffer
+// loads only: a global load to LDS counts as a FLAT access, after which the
+// compiler no longer counts the LDS reads in flight and waits for all of them.
+__device__ __forceinline__ void buffer_to_lds(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff,
+                                              uint16_t* lds) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (LdsPtr)lds, 16, voff, soff, 0, 0);
 }
 
-// Stage kinds (bits 1-2 of a stage's flags): every key from the prefix source,
-// every key from the suffix source (padding keys read suffix row 0), or both.
-constexpr int kStagePrefix = 1, kStageSuffix = 2;
+// What the stage loads of one lane need: its first key of a stage, and the byte
+// column of a K and of a V row it moves (which undoes the LDS permutation) plus
+// the key's offset inside its unit.
+struct LoadLane {
+  int key0, kcol, vcol;
+};
 
-// A stage from one source (the common case) addresses its pieces as 32-bit
-// byte offsets from that source's base, which stays in scalar registers; a
-// stage across the prefix/suffix boundary selects a 64-bit base per piece.
+// Loads the K and V rows of the stage at position pos0 into dk and dv.  base: the
+// unit table entries of this lane's keys; bases/valids: the stage's unit tables.
+// A stage of 64 rows of one source (the common case) goes through one buffer
+// resource per tensor with 32-bit byte offsets.  Any other takes the lanes of
+// the two sources in turn (a key without a row reads its unit's last, or suffix
+// row 0; its weight is forced to 0), and with a source past 4 GiB a resource per
+// group of 4 keys, which share a unit.
 template <int D>
-__device__ __forceinline__ void tile_load(const AttnArgs& a, int g, int kind, const TileKeys<D>& tk,
-                                          TileRegs<D>& r) {
-  const int seg8 = (threadIdx.x % TileRegs<D>::kSegs) * 8;
-  if (a.off32 && kind != (kStagePrefix | kStageSuffix)) {  // uniform
-    const bool pre = kind == kStagePrefix;
+__device__ __forceinline__ void stage_load(const AttnArgs& a, int flags, const int* base,
+                                           const int* bases, const int* valids, int pos0, int wave,
+                                           const LoadLane& ll, uint16_t* dk, uint16_t* dv) {
+  using St = Stage<D>;
+  const int umask = (1 << a.log2u) - 1;
+  dk += wave * St::kRowsPerLoad * D;
+  dv += wave * St::kRowsPerLoad * D;
+  if (a.off32 && (flags & kStageMixed) != kStageMixed) {  // uniform
+    const bool pre = flags & kStagePrefix;
     const uint32_t bytes = pre ? a.pre_bytes : a.suf_bytes;
     const __amdgpu_buffer_rsrc_t kr = raw_rsrc(pre ? a.kbase : a.ks, bytes);
     const __amdgpu_buffer_rsrc_t vr = raw_rsrc(pre ? a.vbase : a.vs, bytes);
-    const uint32_t col = (uint32_t)(g * D + seg8) * 2u;
 #pragma unroll
-    for (int p = 0; p < TileRegs<D>::kPer; ++p) {
-      const uint32_t off = (uint32_t)tk.row[p] + col;  // the table holds byte offsets
-      r.k[p] = __builtin_amdgcn_raw_buffer_load_b128(kr, off, 0, 0);
-      r.v[p] = __builtin_amdgcn_raw_buffer_load_b128(vr, off, 0, 0);
+    for (int p = 0; p < St::kPer; ++p) {
+      const uint32_t soff = (p * St::kKeyStep & umask) * a.row_bytes;
+      buffer_to_lds(kr, (uint32_t)base[p] + (uint32_t)ll.kcol, soff, dk + p * St::kKeyStep * D);
+      buffer_to_lds(vr, (uint32_t)base[p] + (uint32_t)ll.vcol, soff, dv + p * St::kKeyStep * D);
     }
     return;
   }
-  const uint64_t col = (uint64_t)(g * D + seg8);
+  int key0 = ll.key0, kcol = ll.kcol, vcol = ll.vcol;
+  asm volatile("" : "+v"(kcol), "+v"(vcol), "+v"(key0), "+s"(wave));  // nothing is kept across stages
+  // the columns alone: they hold the key's offset inside its unit as well
+  kcol -= (key0 & umask) * (int)a.row_bytes;
+  vcol -= (key0 & umask) * (int)a.row_bytes;
+  if (a.off32) {
+    const __amdgpu_buffer_rsrc_t kp = raw_rsrc(a.kbase, a.pre_bytes), vp = raw_rsrc(a.vbase, a.pre_bytes);
+    const __amdgpu_buffer_rsrc_t ks = raw_rsrc(a.ks, a.suf_bytes), vs = raw_rsrc(a.vs, a.suf_bytes);
+    int valid[St::kPer];
 #pragma unroll
-  for (int p = 0; p < TileRegs<D>::kPer; ++p) {
-    // element offset of the piece: from the table's byte offset, or its row
-    const uint64_t e = a.off32 ? (uint64_t)((uint32_t)tk.row[p] >> 1) + col
-                               : (uint64_t)(uint32_t)tk.row[p] * (uint32_t)(a.Hkv * D) + col;
-    const bool pre = tk.thr[p] == kPrefix;
-    r.k[p] = *reinterpret_cast<const u32x4*>((pre ? a.kbase : a.ks) + e);
-    r.v[p] = *reinterpret_cast<const u32x4*>((pre ? a.vbase : a.vs) + e);
-  }
-}
-
-template <int D>
-__device__ __forceinline__ void tile_store(const TileRegs<D>& r, uint16_t* lk, uint16_t* lv) {
-  constexpr int kSegs = TileRegs<D>::kSegs;
+    for (int p = 0; p < St::kPer; ++p) valid[p] = valids[(key0 + p * St::kKeyStep) >> a.log2u];
 #pragma unroll
-  for (int p = 0; p < TileRegs<D>::kPer; ++p) {
-    const int idx = threadIdx.x + p * kWaves * 64;
-    const int key = idx / kSegs, seg = idx % kSegs;
-    *reinterpret_cast<u32x4*>(lk + key * KLds<D>::kRow + seg * 8) = r.k[p];
-    *reinterpret_cast<u32x4*>(lv + v_off<D>(key, seg)) = r.v[p];
-  }
-}
-
-// Per-lane state of a wave's 32 rows.
-template <int D>
-struct RowState {
-  f32x16 o[D / 32];  // O^T: o[db][v] holds d = 32*db + 8*(v/4) + 4*half + v%4
-  float m_run;       // reference (scaled log2 units), -inf before any
-  float l_run;       // sum of numerators against m_run
-};
-
-// S^T of one stage for this wave's rows: two 32-key products.
-template <int D>
-__device__ __forceinline__ void stage_logits(const uint16_t* lk, int kbase_off,
-                                             const bf16x8 (&qf)[D / 16], f32x16 (&s)[2]) {
-#pragma unroll
-  for (int sub = 0; sub < 2; ++sub)
-#pragma unroll
-    for (int v = 0; v < 16; ++v) s[sub][v] = 0.f;
-#pragma unroll
-  for (int ks = 0; ks < D / 16; ++ks) {
-#pragma unroll
-    for (int sub = 0; sub < 2; ++sub) {
-      const bf16x8 kf = *reinterpret_cast<const bf16x8*>(
-          lk + kbase_off + sub * kSub * KLds<D>::kRow + ks * 16);
-      s[sub] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[ks], s[sub], 0, 0, 0);
-    }
-  }
-}
-
-// Logits of one stage with the keys this lane's query must not see at -inf.
-template <int D>
-__device__ __forceinline__ void stage_masked_logits(const uint16_t* lk, int kbase_off,
-                                                    const bf16x8 (&qf)[D / 16], const int* thrs,
-                                                    bool need_mask, int t, f32x16 (&s)[2]) {
-  const int half = (threadIdx.x >> 5) & 1;
-  stage_logits<D>(lk, kbase_off, qf, s);
-  // register v of product `sub` holds key 32*sub + 16*(v/8) + 8*half + v%8:
-  // runs of 8 consecutive keys, read as two 16-byte words each
-  if (need_mask) {
-#pragma unroll
-    for (int sub = 0; sub < 2; ++sub)
-#pragma unroll
-      for (int v8 = 0; v8 < 2; ++v8) {
-        const int* tp = thrs + kSub * sub + 16 * v8 + 8 * half;
-        const int4 t0 = *reinterpret_cast<const int4*>(tp);
-        const int4 t1 = *reinterpret_cast<const int4*>(tp + 4);
-        const int th[8] = {t0.x, t0.y, t0.z, t0.w, t1.x, t1.y, t1.z, t1.w};
-#pragma unroll
-        for (int e = 0; e < 8; ++e)
-          if (t < th[e]) s[sub][8 * v8 + e] = -INFINITY;
-      }
-  }
-}
-
-// Softmax part of one 64-key stage from the K buffer lk whose visibility
-// thresholds are `thrs`: numerators into s.  The reference moves only when the stage's
-// maximum exceeds it by more than kLazy (log2 units): numerators stay below
-// 2^kLazy, numerator and denominator share the reference, and most stages skip
-// the O rescale.
-template <int D>
-__device__ __forceinline__ void stage_softmax(const AttnArgs& a, const uint16_t* lk, const int* thrs,
-                                              bool need_mask, int t, int kbase_off,
-                                              const bf16x8 (&qf)[D / 16], RowState<D>& rs,
-                                              f32x16 (&s)[2]) {
-  stage_masked_logits<D>(lk, kbase_off, qf, thrs, need_mask, t, s);
-  float mx = fmaxf(s[0][0], s[1][0]);
-#pragma unroll
-  for (int v = 1; v < 16; ++v) mx = fmaxf(mx, fmaxf(s[0][v], s[1][v]));
-  mx = fmaxf(mx, partner_f(mx));
-  const float mt = mx * a.c1;
-  const float m_new = mt > rs.m_run + kLazy ? mt : rs.m_run;
-  const float m_use = m_new == -INFINITY ? 0.f : m_new;
-  const float alpha = __builtin_amdgcn_exp2f(rs.m_run - m_use);
-  float sum = 0.f;
-#pragma unroll
-  for (int sub = 0; sub < 2; ++sub)
-#pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      s[sub][v] = __builtin_amdgcn_exp2f(fmaf(s[sub][v], a.c1, -m_use));
-      sum += s[sub][v];
-    }
-  sum += partner_f(sum);
-  rs.l_run = rs.l_run * alpha + sum;
-  rs.m_run = m_new;
-  if (__any(alpha != 1.f)) {
-#pragma unroll
-    for (int db = 0; db < D / 32; ++db)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) rs.o[db][v] *= alpha;
-  }
-}
-
-// O^T += V^T P^T from the V buffer lv, 16 keys per product.
-template <int D>
-__device__ __forceinline__ void stage_pv(const uint16_t* lv, const int (&voff)[D / 32],
-                                         const f32x16 (&s)[2], RowState<D>& rs) {
-#pragma unroll
-  for (int sub = 0; sub < 2; ++sub) {
-    bf16x8 pb[2];
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-      for (int e = 0; e < 8; ++e) pb[kb][e] = (__bf16)s[sub][8 * kb + e];
-#pragma unroll
-    for (int db = 0; db < D / 32; ++db) {
-#pragma unroll
-      for (int kb = 0; kb < 2; ++kb) {
-        s16x4 piece[2];
-#pragma unroll
-        for (int rd = 0; rd < 2; ++rd)
-          piece[rd] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-              (__attribute__((address_space(3))) s16x4*)(lv + voff[db] +
-                                                         (sub * kSub + 16 * kb + 4 * rd) * D));
-        bf16x8 vf;
-        *reinterpret_cast<s16x4*>(&vf) = piece[0];
-        *(reinterpret_cast<s16x4*>(&vf) + 1) = piece[1];
-        rs.o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pb[kb], rs.o[db], 0, 0, 0);
+    for (int p = 0; p < St::kPer; ++p) {
+      const int key = key0 + p * St::kKeyStep;
+      const uint32_t off = valid[p] > 0 ? (uint32_t)base[p] +
+                                              (uint32_t)min(key & umask, valid[p] - 1) * a.row_bytes
+                                        : 0u;
+      if (valid[p] > 0 && pos0 + key < a.kc) {
+        buffer_to_lds(kp, off + (uint32_t)kcol, 0, dk + p * St::kKeyStep * D);
+        buffer_to_lds(vp, off + (uint32_t)vcol, 0, dv + p * St::kKeyStep * D);
+      } else {
+        buffer_to_lds(ks, off + (uint32_t)kcol, 0, dk + p * St::kKeyStep * D);
+        buffer_to_lds(vs, off + (uint32_t)vcol, 0, dv + p * St::kKeyStep * D);
       }
     }
+    return;
   }
+  constexpr int kGroups = St::kRowsPerLoad / 4, kN = St::kPer * kGroups;
+#pragma unroll 1
+  for (int i = 0; i < kN; ++i) {
+    const int p = i / kGroups, q = i % kGroups;
+    const int gkey = p * St::kKeyStep + wave * St::kRowsPerLoad + 4 * q;  // uniform
+    const int valid = __builtin_amdgcn_readfirstlane(valids[gkey >> a.log2u]);
+    const uint32_t row = (uint32_t)__builtin_amdgcn_readfirstlane(bases[gkey >> a.log2u]);
+    const bool pre = valid > 0 && pos0 + gkey < a.kc;
+    const uint64_t off = valid > 0 ? (uint64_t)row * a.row_bytes : 0;
+    const uint32_t in_unit = (uint32_t)min((key0 + p * St::kKeyStep) & umask, max(valid - 1, 0)) * a.row_bytes;
+    const char* kp = reinterpret_cast<const char*>(pre ? a.kbase : a.ks) + off;
+    const char* vp = reinterpret_cast<const char*>(pre ? a.vbase : a.vs) + off;
+    // (the offsets stay inside one unit: no bound is needed beyond it)
+    if (kGroups == 1 || (int)((threadIdx.x & 63) / (64 / kGroups)) == q) {
+      buffer_to_lds(raw_rsrc(kp, 0xffffffffu), (uint32_t)kcol + in_unit, 0, dk + p * St::kKeyStep * D);
+      buffer_to_lds(raw_rsrc(vp, 0xffffffffu), (uint32_t)vcol + in_unit, 0, dv + p * St::kKeyStep * D);
+    }
+  }
+}
+
+// Every wave's stage loads have landed in LDS (and the LDS reads before this
+// are done): each wave waits for its own, then for the others.
+__device__ __forceinline__ void stage_barrier() {
+  __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0) lgkmcnt(0)
+  __syncthreads();
+}
+
+// K operand fragment ks of 32 keys: kfo is this lane's byte offset of segment
+// `half` of its row; segment 2 ks + half sits at that offset ^ 32 ks.
+template <int D>
+__device__ __forceinline__ bf16x8 read_k(const uint16_t* lk, uint32_t kfo, int sub, int ks) {
+  return *reinterpret_cast<const bf16x8*>(reinterpret_cast<const char*>(lk) + (kfo ^ (32u * ks)) +
+                                          sub * kSub * D * 2);
+}
+
+// V^T operand fragment (kb, db) of 32 keys: voff is the byte offset for db = 0,
+// that of db is voff ^ 64 db, and (sub, kb, rd) add whole rows.
+template <int D>
+__device__ __forceinline__ bf16x8 read_v(const uint16_t* lv, uint32_t voff, int sub, int kb, int db) {
+  bf16x8 vf;
+#pragma unroll
+  for (int rd = 0; rd < 2; ++rd)
+    *(reinterpret_cast<s16x4*>(&vf) + rd) = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+        (__attribute__((address_space(3))) s16x4*)(reinterpret_cast<const char*>(lv) +
+                                                   (voff ^ (64u * db)) +
+                                                   (sub * kSub + 16 * kb + 4 * rd) * D * 2));
+  return vf;
+}
+
+// The numerators exp2(c1 s - m) of 32 keys in 16 / E + 2 steps, which are
+// issued between MFMAs: step i scales the E logits of group i, takes the
+// exponentials of group i - 1, and adds those of group i - 2 to the row's sums
+// and packs them to bf16 pairs (P^T).  The empty asm keeps a step in its place.
+template <int E, int i>
+__device__ __forceinline__ void numerator_step(f32x16& s, float c1, float m, float (&l)[2],
+                                               u32x4 (&pb)[2]) {
+  constexpr int kGroups = 16 / E;
+  if constexpr (i < 0 || i > kGroups + 1) return;
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    if (i < kGroups) s[E * i + e] = fmaf(s[E * i + e], c1, -m);
+    if (i >= 1 && i <= kGroups) s[E * (i - 1) + e] = __builtin_amdgcn_exp2f(s[E * (i - 1) + e]);
+    const int v = E * (i - 2) + e;
+    if (i < 2 || i > kGroups + 1) continue;
+    l[v & 1] += s[v];
+    asm volatile("" : "+v"(l[v & 1]));
+    if (v & 1) {
+      const bf16x2 b = {(__bf16)s[v - 1], (__bf16)s[v]};
+      uint32_t w = __builtin_bit_cast(uint32_t, b);
+      asm volatile("" : "+v"(w));
+      pb[v >> 3][(v & 7) >> 1] = w;
+    }
+  }
+}
+
+// -inf for the keys of product `sub` of the stage at position pos0 that this
+// lane's query t must not see.  Register v holds key 32*sub + 16*(v/8) + 8*half +
+// v%8.
+__device__ __forceinline__ void mask_logits(const AttnArgs& a, const int* valids, int pos0, int sub,
+                                            int t, f32x16& s) {
+  int key_lane = kSub * sub + ((threadIdx.x >> 2) & 8);  // + 8 * half
+  asm volatile("" : "+v"(key_lane));  // nothing of this (rare) path is kept across stages
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {  // 4 keys, inside one unit
+    const int key = key_lane + 16 * (q >> 1) + 4 * (q & 1);
+    int seen = valids[key >> a.log2u] - (key & ((1 << a.log2u) - 1));
+    const int p = pos0 + key - a.kc;  // suffix position
+    if (p >= 0) seen = min(seen, t - p + 1);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) s[4 * q + e] = e < seen ? s[4 * q + e] : -INFINITY;
+  }
+}
+
+__device__ __forceinline__ float max16(const f32x16& s) {
+  float mx = s[0];
+#pragma unroll
+  for (int v = 1; v < 16; ++v) mx = fmaxf(mx, s[v]);
+  return mx;
+}
+
+// f(0), f(1), ... with compile-time arguments.
+template <class F, int... I>
+__device__ __forceinline__ void for_each_of(std::integer_sequence<int, I...>, F&& f) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, class F>
+__device__ __forceinline__ void static_for(F&& f) {
+  for_each_of(std::make_integer_sequence<int, N>{}, f);
 }
 
 template <int D>
 __global__ __launch_bounds__(kWaves * 64, 2) void attn_kernel(AttnArgs a) {
-  __shared__ __attribute__((aligned(16))) uint16_t lk[2][kTile * KLds<D>::kRow];
-  __shared__ __attribute__((aligned(16))) uint16_t lv[2][kTile * D];
-  // key tables of the slice (rows, thresholds), then one flags word per stage:
-  // bit 0 a key some row of the block must not see, bits 1-2 the stage's kind
-  // (dynamic: tiles_per_split * (2 * kTile + 1) ints)
+  using St = Stage<D>;
+  // two stage buffers, as arrays of their own: loads into one are then known
+  // not to touch the other
+  __shared__ __attribute__((aligned(16))) uint16_t k0[kTile * D], k1[kTile * D];
+  __shared__ __attribute__((aligned(16))) uint16_t v0[kTile * D], v1[kTile * D];
+  // unit tables of the slice (base, valid), then one flags word per stage
+  // (dynamic: attn_slice_bytes)
   extern __shared__ int slice_lds[];
-  int* rows = slice_lds;
-  int* thrs = slice_lds + a.tiles_per_split * kTile;
-  int* stage_flags = slice_lds + 2 * a.tiles_per_split * kTile;
+  const int upst = kTile >> a.log2u;  // units per stage
+  int* bases = slice_lds;
+  int* valids = slice_lds + a.tiles_per_split * upst;
+  int* stage_flags = slice_lds + 2 * a.tiles_per_split * upst;
 
   // logical order (g, split, row block): blocks reading the same K/V tiles are
   // adjacent, hence on the same XCD and its L2
@@ -371,7 +395,8 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attn_kernel(AttnArgs a) {
   const int rb = (int)(L % a.n_row_blocks);
   const int split = (int)((L / a.n_row_blocks) % a.n_splits);
   const int g = (int)(L / ((uint32_t)a.n_splits * a.n_row_blocks));
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, half = lane >> 5;
+  const int lane = threadIdx.x & 63, half = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 
   const int row = rb * kBlockRows + wave * kWaveRows + (lane & 31);
   const bool row_ok = row < a.R;
@@ -387,114 +412,229 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attn_kernel(AttnArgs a) {
   const int tile0 = split * a.tiles_per_split;
   const int nt = max(0, min(ntiles, tile0 + a.tiles_per_split) - tile0);
 
-  // key tables of the slice, one stage per wave at a time, and whether a stage
-  // has a key some row of the block must not see; all index loads first
-  constexpr int kMaxIt = kMaxSliceKeys / kTile / kWaves;
-  int jv[kMaxIt], sv[kMaxIt];
-#pragma unroll
-  for (int it = 0; it < kMaxIt; ++it) {
-    const int st = wave + it * kWaves;
-    jv[it] = 0;
-    sv[it] = 0;
-    if (st < nt) key_chunk_loads(a, (tile0 + st) * kTile + lane, jv[it], sv[it]);
-  }
-  // Q after the index loads: loads return in order, so the key tables (on the
-  // critical path to the first K/V loads) do not wait for Q
+  // the first units' index loads, then Q: loads return in order, so the tables
+  // (on the critical path to the first K/V loads) do not wait for Q
+  const int pos00 = tile0 * kTile, n_units = nt * upst;
+  int j0, slot0;
+  unit_chunk(a, (int)threadIdx.x < n_units ? pos00 + ((int)threadIdx.x << a.log2u) : a.kc, j0, slot0);
   bf16x8 qf[D / 16];
   {
     const uint16_t* src = a.q + ((int64_t)(row_ok ? t : 0) * a.Hq + (int64_t)g * a.G + hi) * D + 8 * half;
 #pragma unroll
-    for (int ks = 0; ks < D / 16; ++ks) {
-      u32x4 v = *reinterpret_cast<const u32x4*>(src + 16 * ks);
-      if (!row_ok) v = u32x4{0u, 0u, 0u, 0u};
-      qf[ks] = *reinterpret_cast<bf16x8*>(&v);
+    for (int ks = 0; ks < D / 16; ++ks)
+      qf[ks] = *reinterpret_cast<const bf16x8*>(src + 16 * ks);
+  }
+  // the units of a stage are neighbouring lanes of one wave, the first of which
+  // writes the stage's flags: a unit short of rows makes it mixed and masked
+  for (int i0 = 0; i0 < n_units; i0 += kWaves * 64) {
+    const int i = i0 + (int)threadIdx.x, pos = pos00 + (i << a.log2u);
+    int urow = 0, valid = 0;
+    if (i0 > 0) unit_chunk(a, i < n_units ? pos : a.kc, j0, slot0);
+    if (i < n_units) unit_entry(a, pos, j0, slot0, urow, valid);
+    const uint64_t shortfall = __ballot(valid < (1 << a.log2u)) >> (lane & -upst);
+    if (i < n_units) {
+      // the row's byte offset from its source's base when every one fits in 32 bits
+      bases[i] = a.off32 ? (int)((uint32_t)urow * a.row_bytes) : urow;
+      valids[i] = valid;
+      if ((i & (upst - 1)) == 0) {
+        const int end = pos + kTile - a.kc;  // keys of the stage's end past the prefix
+        int f = (pos < a.kc ? kStagePrefix : 0) | (end > 0 ? kStageSuffix : 0);
+        if (end > 0 && end - 1 > first_t) f |= kStageMask;
+        if (shortfall & ((1ull << upst) - 1)) f |= kStageMixed | kStageMask;
+        stage_flags[(uint32_t)i / (uint32_t)upst] = f;
+      }
     }
   }
+  if (!row_ok) {
 #pragma unroll
-  for (int it = 0; it < kMaxIt; ++it) {
-    const int st = wave + it * kWaves;
-    if (st >= nt) break;  // uniform
-    const int pos = (tile0 + st) * kTile + lane;
-    int krow = 0, kthr = kNever;
-    if (pos < np_block) key_entry(a, pos, jv[it], sv[it], krow, kthr);
-    // the row's byte offset from its source's base when every one fits in 32 bits
-    rows[st * kTile + lane] = a.off32 ? (int)((uint32_t)krow * a.row_bytes) : krow;
-    thrs[st * kTile + lane] = kthr;
-    const uint64_t bad = __ballot(kthr > first_t), pre = __ballot(kthr == kPrefix);
-    if (lane == 0)
-      stage_flags[st] = (bad != 0 ? 1 : 0) | (pre != 0 ? kStagePrefix << 1 : 0) |
-                        (pre != ~0ull ? kStageSuffix << 1 : 0);
+    for (int ks = 0; ks < D / 16; ++ks) qf[ks] = __builtin_bit_cast(bf16x8, u32x4{0u, 0u, 0u, 0u});
   }
   __syncthreads();
-  auto stage_kind = [&](int st) { return __builtin_amdgcn_readfirstlane(stage_flags[st] >> 1); };
 
-  // per-lane LDS element offsets of the operand reads (the same for every stage)
-  const int kbase_off = kappa(lane & 31) * KLds<D>::kRow + 8 * half;
+  // this lane's keys and byte columns of the stage loads
+  LoadLane ll;
+  {
+    ll.key0 = wave * St::kRowsPerLoad + lane / St::kSegs;
+    const int seg = lane % St::kSegs, in_unit = (ll.key0 & ((1 << a.log2u) - 1)) * (int)a.row_bytes;
+    ll.kcol = 2 * (g * D + ((seg ^ k_swz<D>(ll.key0)) << 3)) + in_unit;
+    ll.vcol = 2 * (g * D + ((seg ^ v_swz<D>(ll.key0)) << 3)) + in_unit;
+  }
+  const int* lane_bases = bases + (ll.key0 >> a.log2u);
+  // byte offsets of the operand reads (the same for every stage)
+  const int kr = kappa(lane & 31);
+  const uint32_t kfo = 2 * (kr * D + ((half ^ k_swz<D>(kr)) << 3));
   // V^T fragment pieces: lane (group g4 = (lane/16)%2, s16 = lane%16) supplies
   // row 16*kb + 8*half + 4*rd + s16/4, columns 32*db + 16*g4 + 4*(s16%4) .. +3.
-  // The swizzle depends on the row modulo 4 only, so (kb, rd) add whole rows:
-  // voff[db] is the offset for kb = rd = 0 and the rest are immediate offsets.
+  // The swizzle depends on the row modulo 4 only.
   const int s16 = lane & 15, g4 = (lane >> 4) & 1;
-  int voff[D / 32];
-#pragma unroll
-  for (int db = 0; db < D / 32; ++db) {
-    const int vrow = 8 * half + (s16 >> 2);
-    const int col = 32 * db + 16 * g4 + 4 * (s16 & 3);
-    voff[db] = v_off<D>(vrow, col >> 3) + (col & 7);
-  }
+  const uint32_t voff = 2 * (v_off<D>(8 * half + (s16 >> 2), 2 * g4 + ((s16 & 3) >> 1)) + 4 * (s16 & 1));
 
-  RowState<D> rs;
+  constexpr int kG = D / 16;  // MFMAs of one 32-key product, and of one O update
+  constexpr int kE = 256 / D; // logits per numerator step: kG + 2 steps per half
+  f32x16 o[D / 32];
+  float l[2];
+  float ref = 0.f;  // reference of this lane's row (scaled log2 units)
+  auto flags_of = [&](int st) { return __builtin_amdgcn_readfirstlane(stage_flags[st]); };
+  // the unit table entries of this lane's keys of a stage
+  auto read_bases = [&](int st, int* r) {
 #pragma unroll
-  for (int db = 0; db < D / 32; ++db)
-#pragma unroll
-    for (int v = 0; v < 16; ++v) rs.o[db][v] = 0.f;
-  rs.m_run = -INFINITY;
-  rs.l_run = 0.f;
+    for (int p = 0; p < St::kPer; ++p) r[p] = lane_bases[st * upst + (p * St::kKeyStep >> a.log2u)];
+  };
+  auto load_stage = [&](int st, int f, const int* r, uint16_t* dk, uint16_t* dv) {
+    stage_load<D>(a, f, r, bases + st * upst, valids + st * upst, pos00 + st * kTile, wave, ll, dk, dv);
+  };
+  auto mask = [&](int st, int sub, f32x16& s) {
+    mask_logits(a, valids + st * upst, pos00 + st * kTile, sub, t, s);
+  };
 
-  TileRegs<D> regs;
-  TileKeys<D> tk;
-  if (nt > 0) {
-    tile_keys<D>(rows, thrs, tk);
-    tile_load<D>(a, g, stage_kind(0), tk, regs);
-    if (nt > 1) tile_keys<D>(rows + kTile, thrs + kTile, tk);
-    tile_store<D>(regs, lk[0], lv[0]);
-    __syncthreads();
-  }
-  for (int st = 0; st < nt; ++st) {
-    const int cur = st & 1;
-    const bool has_next = st + 1 < nt;
-    // the next stage's K/V rows load during this stage; the table entries of
-    // the stage after it are read now, for the next iteration
-    if (has_next) {
-      tile_load<D>(a, g, stage_kind(st + 1), tk, regs);
-      if (st + 2 < nt) tile_keys<D>(rows + (st + 2) * kTile, thrs + (st + 2) * kTile, tk);
+  bool no_ref = false;  // the reference had to be taken from no key at all
+  for (int attempt = 0;; ++attempt) {
+#pragma unroll
+    for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) o[db][v] = 0.f;
+    l[0] = l[1] = 0.f;
+    if (nt > 0) {
+      int r[St::kPer];
+      read_bases(0, r);
+      int fl = flags_of(0);  // of the current stage
+      load_stage(0, fl, r, k0, v0);
+      stage_barrier();
+      bf16x8 ka[kG];  // K fragments of the current stage's first 32 keys
+#pragma unroll
+      for (int i = 0; i < kG; ++i) ka[i] = read_k<D>(k0, kfo, 0, i);
+
+      // One stage (K in lk, V in lv), with the next one's rows loading into nk and
+      // nv, as four runs of kG MFMAs: the first half's product, the second half's
+      // product beside the first half's numerators, the first half's O update
+      // beside the second half's numerators, and the second half's O update; each
+      // run reads the operands of the next.  The order inside a run is fixed by
+      // scheduling barriers: left to itself the compiler reads each operand right
+      // before its MFMA, which then waits for it.
+      auto stage = [&](int st, uint16_t* lk, uint16_t* lv, uint16_t* nk, uint16_t* nv)
+          __attribute__((always_inline)) {
+        // the operand offsets stay opaque here, so that each buffer's address is
+        // an immediate of the read and not a register of its own
+        uint32_t ko = kfo, vo = voff;
+        asm volatile("" : "+v"(ko), "+v"(vo));
+        int fn = 0;
+        if (st + 1 < nt) {
+          read_bases(st + 1, r);
+          fn = flags_of(st + 1);
+          load_stage(st + 1, fn, r, nk, nv);
+        }
+        bf16x8 kb[kG], va[2][D / 32], vb[2][D / 32];
+        f32x16 s0, s1;
+        u32x4 p0[2], p1[2];
+#pragma unroll
+        for (int v = 0; v < 16; ++v) s0[v] = s1[v] = 0.f;
+        __builtin_amdgcn_sched_barrier(0);
+        static_for<kG>([&](auto i) __attribute__((always_inline)) {
+          kb[i] = read_k<D>(lk, ko, 1, i);
+          s0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[i], qf[i], s0, 0, 0, 0);
+          __builtin_amdgcn_sched_barrier(0);
+        });
+        if (fl & kStageMask) mask(st, 0, s0);
+        if (st == 0 && attempt == 0) {  // the reference: the first 32 keys' largest logit
+          float mx = max16(s0);
+          mx = fmaxf(mx, partner_f(mx));
+          no_ref = mx == -INFINITY;
+          ref = no_ref ? 0.f : mx * a.c1;
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        static_for<kG>([&](auto i) __attribute__((always_inline)) {
+          constexpr int kk = i / (D / 32), db = i % (D / 32);
+          va[kk][db] = read_v<D>(lv, vo, 0, kk, db);
+          s1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kb[i], qf[i], s1, 0, 0, 0);
+          numerator_step<kE, i>(s0, a.c1, ref, l, p0);
+          __builtin_amdgcn_sched_barrier(0);
+        });
+        if (fl & kStageMask) mask(st, 1, s1);
+        __builtin_amdgcn_sched_barrier(0);
+        static_for<kG>([&](auto i) __attribute__((always_inline)) {
+          constexpr int kk = i / (D / 32), db = i % (D / 32);
+          vb[kk][db] = read_v<D>(lv, vo, 1, kk, db);
+          if constexpr (i < 2) numerator_step<kE, kG + i>(s0, a.c1, ref, l, p0);
+          o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[kk][db], __builtin_bit_cast(bf16x8, p0[kk]),
+                                                          o[db], 0, 0, 0);
+          numerator_step<kE, i>(s1, a.c1, ref, l, p1);
+          __builtin_amdgcn_sched_barrier(0);
+        });
+        stage_barrier();  // the next stage has landed; this one's buffers are read
+        __builtin_amdgcn_sched_barrier(0);
+        static_for<kG>([&](auto i) __attribute__((always_inline)) {
+          constexpr int kk = i / (D / 32), db = i % (D / 32);
+          ka[i] = read_k<D>(nk, ko, 0, i);  // (after the last stage: read and not used)
+          if constexpr (i < 2) numerator_step<kE, kG + i>(s1, a.c1, ref, l, p1);
+          o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vb[kk][db], __builtin_bit_cast(bf16x8, p1[kk]),
+                                                          o[db], 0, 0, 0);
+          __builtin_amdgcn_sched_barrier(0);
+        });
+        fl = fn;
+      };
+      for (int st = 0; st < nt; st += 2) {
+        stage(st, k0, v0, k1, v1);
+        if (st + 1 >= nt) break;
+        stage(st + 1, k1, v1, k0, v0);
+      }
     }
-    f32x16 s[2];
-    stage_softmax<D>(a, lk[cur], thrs + st * kTile, stage_flags[st] & 1, t, kbase_off, qf, rs, s);
-    stage_pv<D>(lv[cur], voff, s, rs);
-    if (has_next) {
-      tile_store<D>(regs, lk[cur ^ 1], lv[cur ^ 1]);
+    l[0] += l[1];
+    l[0] += partner_f(l[0]);
+    // The reference is the first keys' maximum: a later logit far above it can
+    // push the sum past the guard or an output past fp32, and a row whose first
+    // keys are all hidden has none.  Then once more, against the slice's own
+    // maximum.
+    if (attempt) break;
+    // (a sum over the outputs is inf or NaN if one of them is)
+    float any[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) any[v & 3] += o[db][v];
+    const uint32_t total = __float_as_uint((any[0] + any[1]) + (any[2] + any[3]));
+    const bool bad = (total & 0x7f800000u) == 0x7f800000u ||
+                     (__float_as_uint(l[0]) & 0x7fffffffu) > __float_as_uint(kGuard) ||
+                     (no_ref && l[0] < 1.f / kGuard);
+    if (!__syncthreads_or(bad)) break;
+    float mx = -INFINITY;
+    for (int st = 0; st < nt; ++st) {
+      int r[St::kPer];
+      read_bases(st, r);
+      const int f = flags_of(st);
+      load_stage(st, f, r, k0, v0);
+      stage_barrier();
+#pragma unroll
+      for (int sub = 0; sub < 2; ++sub) {
+        f32x16 s;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) s[v] = 0.f;
+#pragma unroll
+        for (int i = 0; i < kG; ++i)
+          s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(read_k<D>(k0, kfo, sub, i), qf[i], s, 0, 0, 0);
+        mask(st, sub, s);
+        mx = fmaxf(mx, max16(s));
+      }
       __syncthreads();
     }
+    mx = fmaxf(mx, partner_f(mx));
+    ref = mx == -INFINITY ? 0.f : mx * a.c1;
   }
 
   // Output rows through LDS, so that every global store is a whole 16-byte
   // piece of a row and 16 lanes cover a row: the wave's 32 rows (O/l in
-  // bf16) go to its own slice of the K stage buffer, which every wave has
-  // finished reading after this barrier.
-  __syncthreads();
+  // bf16) go to a stage buffer of its own, which every wave has finished
+  // reading (the barrier above).
   {
-    constexpr int kRow = KLds<D>::kRow;
-    uint16_t* tile = reinterpret_cast<uint16_t*>(lk) + wave * kWaveRows * kRow;
-    const float inv = rs.l_run > 0.f ? 1.f / rs.l_run : 0.f;
-    // o[db][v] holds d = 32*db + 8*(v/4) + 4*half + v%4 of this lane's row
+    constexpr int kRow = D + 8;
+    uint16_t* tile = wave == 0 ? k0 : wave == 1 ? k1 : wave == 2 ? v0 : v1;
+    const float inv = l[0] > 0.f ? 1.f / l[0] : 0.f;
 #pragma unroll
     for (int db = 0; db < D / 32; ++db)
 #pragma unroll
       for (int q4 = 0; q4 < 4; ++q4) {
         __bf16 b[4];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) b[j] = (__bf16)(rs.o[db][4 * q4 + j] * inv);
+        for (int j = 0; j < 4; ++j) b[j] = (__bf16)(o[db][4 * q4 + j] * inv);
         *reinterpret_cast<uint2*>(tile + (lane & 31) * kRow + 32 * db + 8 * q4 + 4 * half) =
             *reinterpret_cast<uint2*>(b);
       }
@@ -502,25 +642,20 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attn_kernel(AttnArgs a) {
     constexpr int kSegs = D / 8, kRowsPerPass = 64 / kSegs;
     const int seg = lane % kSegs;
     const int row_base = rb * kBlockRows + wave * kWaveRows;
+    // output row of this lane's query row; row rr's is lane rr's
+    const int out_row = a.partial ? row : (row_ok ? t : 0) * a.Hq + g * a.G + hi;
+    uint16_t* obase = a.partial ? a.o_part + ((int64_t)split * a.Hkv + g) * a.R * D : a.out;
 #pragma unroll
     for (int r0 = 0; r0 < kWaveRows; r0 += kRowsPerPass) {
       const int rr = r0 + lane / kSegs;
-      const int orow = row_base + rr;
       const uint4 v = *reinterpret_cast<const uint4*>(tile + rr * kRow + seg * 8);
-      if (orow < a.R) {
-        uint16_t* dst;
-        if (!a.partial)
-          dst = a.out + ((int64_t)(orow / a.G) * a.Hq + (int64_t)g * a.G + orow % a.G) * D;
-        else
-          dst = a.o_part + (((int64_t)split * a.Hkv + g) * a.R + orow) * D;
-        *reinterpret_cast<uint4*>(dst + seg * 8) = v;
-      }
+      const int orow = __shfl(out_row, rr);
+      if (row_base + rr < a.R) *reinterpret_cast<uint4*>(obase + (int64_t)orow * D + seg * 8) = v;
     }
   }
   // the reference the numerators were taken against (0 while no key was seen)
   if (a.partial && row_ok && half == 0)
-    a.ml_part[((int64_t)split * a.Hkv + g) * a.R + row] =
-        make_float2(rs.m_run == -INFINITY ? 0.f : rs.m_run, rs.l_run);
+    a.ml_part[((int64_t)split * a.Hkv + g) * a.R + row] = make_float2(ref, l[0]);
 }
 
 // Merges the splits of each row in split order: out = sum_s w_s Ohat_s with
@@ -670,6 +805,19 @@ __global__ __launch_bounds__(64) void attn_f32_kernel(AttnArgsF32 a) {
 
 }  // namespace
 
+namespace {
+
+// Keys of a unit (see kMaxSliceUnits), as a power of two: c is 4, 8, 16 or a
+// multiple of 32.
+int log2_unit(int c) { return c < 32 ? __builtin_ctz(c) : 5; }
+
+// Stages whose tables fit a workgroup's share of the LDS.
+int64_t max_slice_stages(int c) {
+  return std::min<int64_t>(kMaxSliceStages, kMaxSliceUnits / (kTile >> log2_unit(c)));
+}
+
+}  // namespace
+
 AttnPlan make_attn_plan(const ckv_dims* d, int64_t k, bool with_suffix) {
   AttnPlan p{};
   const int G = d->n_q_heads / d->n_kv_heads;
@@ -681,13 +829,32 @@ AttnPlan make_attn_plan(const ckv_dims* d, int64_t k, bool with_suffix) {
   const int64_t np = k * d->chunk_size + (with_suffix ? d->n_suffix : 0);
   const int64_t ntiles = std::max<int64_t>(1, ceil_div(np, kTile));  // no keys: one empty split
   const int64_t base = (int64_t)d->n_kv_heads * ceil_div(p.rows, kBlockRows);
-  // at most ~2 workgroups per CU, keeping >= 4 stages per split and no more
-  // keys per split than the workgroup's code table holds; then the fewest
-  // splits that give the same stages per split
-  int64_t splits = std::max<int64_t>(1, 512 / base);
-  splits = std::min<int64_t>(splits, std::max<int64_t>(1, ntiles / 4));
-  splits = std::max<int64_t>(splits, ceil_div(ntiles, kMaxSliceKeys / kTile));
-  splits = ceil_div(ntiles, ceil_div(ntiles, splits));
+  // The splits that cost least by a model of the launch, in cycles at 1.85 GHz:
+  // 512 workgroups run at once, two per CU, each for its stages (two of them
+  // take 3,440 cycles per stage, one alone on its CU 2,100) and a fixed part
+  // (tables, first loads, output); and every split's partials are merged (14
+  // splits of 40,960 rows took 25 us, 3 of them 8).  At most the splits that
+  // give 512 workgroups of 4 stages or more, or that hold a slice to 16 stages:
+  // more never won, and the partials' workspace stays within that of those.
+  constexpr double kFixed = 15000, kStage = 3440, kFixedAlone = 12500, kStageAlone = 2100;
+  constexpr double kCombine = 5500, kMergeBytes = 5000;
+  const double merge = (double)d->n_kv_heads * p.rows * d->head_dim * 2 / kMergeBytes;
+  const int64_t n_min = ceil_div(ntiles, max_slice_stages(d->chunk_size));
+  const int64_t n_max = std::max(std::max<int64_t>(1, std::min(512 / base, ntiles / 4)),
+                                 ceil_div(ntiles, 16));
+  int64_t splits = 0;
+  double best = 0;
+  for (int64_t n0 = n_min; n0 <= n_max; ++n0) {
+    const int64_t per = ceil_div(ntiles, n0), n = ceil_div(ntiles, per), wgs = base * n, rem = wgs % 512;
+    double cost = (double)(wgs / 512) * (kFixed + kStage * (double)per);
+    if (rem > 0)
+      cost += rem <= 256 ? kFixedAlone + kStageAlone * (double)per : kFixed + kStage * (double)per;
+    if (n > 1) cost += kCombine + merge * (double)n;
+    if (!splits || cost < best) {
+      best = cost;
+      splits = n;
+    }
+  }
   p.n_splits = (int32_t)splits;
   size_t off = 0;
   if (splits > 1) {
@@ -737,6 +904,7 @@ ckv_status attn_args(const ckv_dims* d, const void* q, const ChunkSource& src, c
   a.m = ceil_div(d->n_prefix, d->chunk_size);
   a.c = d->chunk_size;
   a.log2c = (d->chunk_size & (d->chunk_size - 1)) == 0 ? __builtin_ctz(d->chunk_size) : -1;
+  a.log2u = log2_unit(d->chunk_size);
   a.ks = static_cast<const uint16_t*>(k_suffix);
   a.vs = static_cast<const uint16_t*>(v_suffix);
   a.S = d->n_suffix; a.Hq = d->n_q_heads; a.Hkv = d->n_kv_heads;
@@ -744,7 +912,7 @@ ckv_status attn_args(const ckv_dims* d, const void* q, const ChunkSource& src, c
   a.n_splits = n_splits;
   a.with_suffix = with_suffix ? 1 : 0;
   const int64_t ntiles = ceil_div(a.kc + (with_suffix ? a.S : 0), kTile);
-  a.tiles_per_split = (int)ceil_div(ntiles, n_splits);  // <= kMaxSliceKeys / kTile
+  a.tiles_per_split = (int)ceil_div(ntiles, n_splits);  // <= max_slice_stages
   a.n_row_blocks = (int)ceil_div(a.R, kBlockRows);
   a.c1 = resolve_scale(d) * 1.4426950408889634f;
   a.nblocks = (uint32_t)((int64_t)a.Hkv * a.n_row_blocks * a.n_splits);
@@ -753,7 +921,7 @@ ckv_status attn_args(const ckv_dims* d, const void* q, const ChunkSource& src, c
 }
 
 ckv_status launch_attn_kernel(const ckv_dims* d, const AttnArgs& a, hipStream_t st) {
-  const size_t slice_bytes = (size_t)a.tiles_per_split * (2 * kTile + 1) * sizeof(int);
+  const size_t slice_bytes = (size_t)a.tiles_per_split * (2 * (kTile >> a.log2u) + 1) * sizeof(int);
   if (d->head_dim == 128)
     hipLaunchKernelGGL(attn_kernel<128>, dim3(a.nblocks_padded), dim3(kWaves * 64), slice_bytes, st, a);
   else

@@ -32,6 +32,7 @@ void clear_error();
   } while (0)
 
 // ---- vector types ----------------------------------------------------------
+typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
@@ -173,6 +174,7 @@ ckv_status launch_gather(const ckv_dims* d, const void* k_src, const void* v_src
 struct AttnPlan {
   int32_t rows;      // G*S rows per KV head
   int32_t n_splits;  // key splits (1: no combine)
+
   size_t off_o, off_ml, bytes;
 };
 // Keys: the k kept chunks, then (with_suffix) the causal suffix.
