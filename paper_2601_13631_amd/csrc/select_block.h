@@ -1,6 +1,5 @@
 // select_block.h -- top-k ContiguousChunk selection (Sec. 4.4) by one
-// workgroup of THREADS threads (a multiple of 64; one wave suits small m, where
-// the workgroup barriers then cost almost nothing).
+// workgroup of THREADS threads (a multiple of 256).
 //
 // Keeps the k largest of m fp64 chunk scores under the total order (score
 // descending, index ascending) and writes their indices in ascending order.
@@ -14,9 +13,7 @@
 // is an in-order compaction with one block-wide exclusive scan (the counts of
 // greater and of equal keys packed in one 64-bit word), so the indices come
 // out ascending.  Every count is an integer (LDS atomics): the result depends
-// only on the score bits.  With a key cache (LDS, m entries) the scores are
-// read from global memory once; without one, every pass re-reads them (they
-// stay in L2).
+// only on the score bits.  Every pass re-reads the scores (they stay in L2).
 
 #pragma once
 
@@ -24,7 +21,7 @@
 
 namespace ckv {
 
-constexpr int kSelMaxWaves = 4;
+constexpr int kSelMaxWaves = 16;
 
 __device__ __forceinline__ uint64_t order_key(double x) {
   uint64_t u = (uint64_t)__double_as_longlong(x);
@@ -85,23 +82,22 @@ __device__ __forceinline__ int64_t sel_block_exclusive_scan(int64_t v, SelShared
   return before + x - v;
 }
 
-// Called by all THREADS threads of the workgroup; 1 <= k <= m.  cache:
-// nullptr, or LDS room for m keys.
+// Called by all THREADS threads of the workgroup; 1 <= k <= m.  The k indices go
+// to sel and, when sel_copy is not null, to sel_copy too.
 template <int THREADS>
 __device__ __forceinline__ void select_topk_block(const double* scores, int64_t m, int64_t k,
-                                                  int32_t* sel, SelShared& sh, uint64_t* cache) {
-  static_assert(THREADS % 64 == 0 && THREADS <= 64 * kSelMaxWaves, "1 to 4 waves");
+                                                  int32_t* sel, int32_t* sel_copy, SelShared& sh) {
+  static_assert(THREADS % 256 == 0 && THREADS <= 64 * kSelMaxWaves, "4 to 16 waves");
   const int tid = threadIdx.x;
-  auto key_at = [&](int64_t i) -> uint64_t { return cache ? cache[i] : order_key(scores[i]); };
+  auto key_at = [&](int64_t i) -> uint64_t { return order_key(scores[i]); };
   {
     uint64_t lo = ~0ull, hi = 0;
     for (int64_t i = tid; i < m; i += THREADS) {
-      const uint64_t x = order_key(scores[i]);
-      if (cache) cache[i] = x;
+      const uint64_t x = key_at(i);
       lo = x < lo ? x : lo;
       hi = x > hi ? x : hi;
     }
-    sel_block_minmax<THREADS>(lo, hi, sh);  // its barriers also publish the cache
+    sel_block_minmax<THREADS>(lo, hi, sh);
   }
   if (tid == 0) {
     sh.prefix = 0;
@@ -128,41 +124,28 @@ __device__ __forceinline__ void select_topk_block(const double* scores, int64_t 
     }
     __syncthreads();
     // count of candidates in bins >= b as an inclusive scan over t = 255 - b
-    // (thread i holds t = i*kPer .. i*kPer+kPer-1); the bin where that count
-    // first reaches `need` is chosen (one thread)
-    constexpr int kPer = 256 / THREADS;
+    // (thread t < 256 holds bin 255 - t); the bin where that count first reaches
+    // `need` is chosen (one thread)
     const int64_t need = sh.remaining;
-    uint32_t cnt[kPer];
-    uint32_t own = 0;
-#pragma unroll
-    for (int q = 0; q < kPer; ++q) {
-      cnt[q] = sh.hist[255 - (tid * kPer + q)];
-      own += cnt[q];
-    }
-    uint32_t cum = own;
+    const uint32_t cnt = tid < 256 ? sh.hist[255 - tid] : 0;
+    uint32_t cum = cnt;
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) {
       const uint32_t y = __shfl_up(cum, off);
       if ((tid & 63) >= off) cum += y;
     }
-    if (THREADS > 64) {
-      if ((tid & 63) == 63) sh.wsum[tid >> 6] = cum;
-      __syncthreads();
+    if ((tid & 63) == 63 && tid < 256) sh.wsum[tid >> 6] = cum;
+    __syncthreads();
+    if (tid < 256) {
       for (int w = 0; w < (tid >> 6); ++w) cum += sh.wsum[w];
-    }
-    uint32_t before = cum - own;
-#pragma unroll
-    for (int q = 0; q < kPer; ++q) {
-      const uint32_t after = before + cnt[q];
-      if (before < need && after >= need) {
-        const int b = 255 - (tid * kPer + q);
+      const uint32_t before = cum - cnt;
+      if (before < need && cum >= need) {
         const uint64_t keep_hi = shift + 8 >= 64 ? 0 : ~((1ull << (shift + 8)) - 1);
-        sh.prefix = (lo & keep_hi) | ((uint64_t)b << shift);
+        sh.prefix = (lo & keep_hi) | ((uint64_t)(255 - tid) << shift);
         sh.mask = keep_hi | (255ull << shift);
         sh.remaining = need - before;
-        sh.done = (cnt[q] == (uint32_t)sh.remaining) || shift == 0;
+        sh.done = (cnt == (uint32_t)sh.remaining) || shift == 0;
       }
-      before = after;
     }
     __syncthreads();
     if (sh.done) break;
@@ -203,7 +186,11 @@ __device__ __forceinline__ void select_topk_block(const double* scores, int64_t 
     const uint64_t x = key_at(i) & mask;
     bool take = x > prefix;
     if (x == prefix) take = eq_rank++ < remaining;
-    if (take) sel[pos++] = (int32_t)i;
+    if (take) {
+      sel[pos] = (int32_t)i;
+      if (sel_copy) sel_copy[pos] = (int32_t)i;
+      ++pos;
+    }
   }
 }
 

@@ -21,7 +21,12 @@
 
 namespace ckv {
 
-template <int THREADS>
+// Up to this many keys per thread, a thread holds consecutive scores; with more,
+// thread t holds scores t, t + THREADS, ... (a wave's loads are then contiguous:
+// 16 scores per thread side by side are 64 cache lines per load instruction).
+constexpr int kSelConsecutive = 8;
+
+template <int THREADS, int E>
 struct RegSelShared {
   static constexpr int kWaves = THREADS / 64;
   uint32_t whist[kWaves][16];  // per-wave digit counts of the round
@@ -29,6 +34,8 @@ struct RegSelShared {
   uint32_t wgt[kWaves], weq[kWaves];
   uint64_t prefix, mask;
   int32_t remaining, done;
+  // counts of greater (low half) and of equal keys per (key of the thread, wave)
+  uint32_t part[E > kSelConsecutive ? E * kWaves : 1];
 };
 
 __device__ __forceinline__ void minmax_with(uint64_t& lo, uint64_t& hi, uint64_t plo, uint64_t phi) {
@@ -67,27 +74,39 @@ __device__ __forceinline__ uint32_t pair_sum32(uint32_t x) {
 }
 
 // The wave's count of keys per digit value 0..15 (digit 16: not a candidate),
-// for E keys per lane: each lane counts its digits in
-// 4-bit fields of one 64-bit word (E <= 15), the fields are spread to bytes
-// and summed over each row of 16 lanes by DPP (at most 16 * E <= 255), then
-// widened to 16-bit fields and summed over the four rows by the permlane
-// swaps.  Lane 15 returns digit pair (2i, 2i + 1) in cnt[i] (low, high half).
+// for E keys per lane: each lane counts its digits in 4-bit fields of one 64-bit
+// word per kGroup keys, the fields are spread to bytes (and added up over the
+// groups), and summed over each row of 16 lanes by DPP, in bytes while 16 * E <=
+// 255, else widened to 16-bit fields first, then over the four rows by the
+// permlane swaps.  Lane 15 returns digit pair (2i, 2i + 1) in cnt[i] (low, high
+// half).
 template <int E>
 __device__ __forceinline__ void wave_digit_counts(const int (&cd)[E], uint32_t (&cnt)[8]) {
-  static_assert(E <= 15, "4-bit per-lane fields");
-  uint64_t acc = 0;
-#pragma unroll
-  for (int e = 0; e < E; ++e) acc += cd[e] < 16 ? 1ull << (4 * cd[e]) : 0ull;
-  const uint32_t lo = (uint32_t)acc, hi = (uint32_t)(acc >> 32);
+  constexpr int kGroup = E <= 15 ? E : 8;
+  static_assert(E % kGroup == 0 && E <= 128, "4-bit per-lane fields, byte sums");
   // byte j of by[q]: digit 8 * (q / 2) + 2 * j + (q % 2)
-  uint32_t by[4] = {lo & 0x0F0F0F0Fu, (lo >> 4) & 0x0F0F0F0Fu, hi & 0x0F0F0F0Fu,
-                    (hi >> 4) & 0x0F0F0F0Fu};
+  uint32_t by[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {  // inclusive sums along the row: lane 15 holds the row's
-    by[q] += dpp32<kDppRowShr1>(by[q]);
-    by[q] += dpp32<kDppRowShr2>(by[q]);
-    by[q] += dpp32<kDppRowShr4>(by[q]);
-    by[q] += dpp32<kDppRowShr8>(by[q]);
+  for (int e0 = 0; e0 < E; e0 += kGroup) {
+    uint64_t acc = 0;
+#pragma unroll
+    for (int e = e0; e < e0 + kGroup; ++e) acc += cd[e] < 16 ? 1ull << (4 * cd[e]) : 0ull;
+    const uint32_t lo = (uint32_t)acc, hi = (uint32_t)(acc >> 32);
+    by[0] += lo & 0x0F0F0F0Fu;
+    by[1] += (lo >> 4) & 0x0F0F0F0Fu;
+    by[2] += hi & 0x0F0F0F0Fu;
+    by[3] += (hi >> 4) & 0x0F0F0F0Fu;
+  }
+  auto row_sum = [](uint32_t x) __attribute__((always_inline)) {  // inclusive: lane 15 holds the row's
+    x += dpp32<kDppRowShr1>(x);
+    x += dpp32<kDppRowShr2>(x);
+    x += dpp32<kDppRowShr4>(x);
+    x += dpp32<kDppRowShr8>(x);
+    return x;
+  };
+  if constexpr (E <= 15) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) by[q] = row_sum(by[q]);
   }
   // 16-bit fields: cnt[i] = (digit 2i, digit 2i + 1); by[q] byte j is digit
   // 8 * (q / 2) + 2 * j + (q % 2), so digit pair i = 4 * (q / 2) + j comes from
@@ -97,27 +116,31 @@ __device__ __forceinline__ void wave_digit_counts(const int (&cd)[E], uint32_t (
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       const uint32_t ev = (by[2 * h] >> (8 * j)) & 0xFFu, od = (by[2 * h + 1] >> (8 * j)) & 0xFFu;
-      cnt[4 * h + j] = pair_sum32(pair_sum16(ev | (od << 16)));
+      uint32_t x = ev | (od << 16);
+      if constexpr (E > 15) x = row_sum(x);
+      cnt[4 * h + j] = pair_sum32(pair_sum16(x));
     }
 }
 
-// Called by all THREADS threads; m <= E * THREADS, 1 <= k <= m, 4 <= E <= 15.  Thread t
-// holds scores t*E .. t*E+E-1.  The k indices go to out0[0..k) and, when
-// out1 is not null, to out1 too (each thread writes its own kept indices).
+// Called by all THREADS threads; m <= E * THREADS <= 32768, 1 <= k <= m.  The k
+// indices go to out0[0..k) and, when out1 is not null, to out1 too (each thread
+// writes its own kept indices).
 template <int THREADS, int E>
 __device__ __forceinline__ void select_topk_regs(const double* __restrict__ scores, int m, int k,
-                                                 RegSelShared<THREADS>& sh, int32_t* out0,
+                                                 RegSelShared<THREADS, E>& sh, int32_t* out0,
                                                  int32_t* out1) {
-  static_assert(E >= 4 && E <= 15, "keys per thread");
+  static_assert(E >= 4 && E <= 32 && E * THREADS <= 32768, "keys per thread");
   constexpr int kWaves = THREADS / 64;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  constexpr bool kStrided = E > kSelConsecutive;
   const int i0 = tid * E;
   uint64_t x[E];
   bool valid[E];
 #pragma unroll
   for (int e = 0; e < E; ++e) {
-    valid[e] = i0 + e < m;
-    x[e] = order_key(scores[min(i0 + e, m - 1)]);  // unconditional load
+    const int i = kStrided ? e * THREADS + tid : i0 + e;
+    valid[e] = i < m;
+    x[e] = order_key(scores[min(i, m - 1)]);  // unconditional load
   }
   uint64_t lo = ~0ull, hi = 0;
 #pragma unroll
@@ -198,8 +221,56 @@ __device__ __forceinline__ void select_topk_regs(const double* __restrict__ scor
   // among the first `remaining` equal keys by index.  Counts of greater and of
   // equal keys before this thread's first key: wave ballots, then the waves
   // before it (one barrier).
-  bool gt[E], eq[E];
   const uint64_t below = (1ull << lane) - 1;
+  if constexpr (kStrided) {
+    // index order is (e, thread): the waves' counts per e, an exclusive scan of
+    // them by wave 0 (both counts in one word: each is at most 32768), then every
+    // thread's own rank
+    constexpr int kPer = E * kWaves / 64;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const uint64_t xm = x[e] & mask;
+      const uint64_t bg = __ballot(valid[e] && xm > prefix), be = __ballot(valid[e] && xm == prefix);
+      if (lane == 0) sh.part[e * kWaves + wave] = __popcll(bg) | ((uint32_t)__popcll(be) << 16);
+    }
+    __syncthreads();
+    if (wave == 0) {
+      uint32_t c[kPer], own = 0;
+#pragma unroll
+      for (int i = 0; i < kPer; ++i) {
+        c[i] = sh.part[lane * kPer + i];
+        own += c[i];
+      }
+      uint32_t cum = own;
+#pragma unroll
+      for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t y = __shfl_up(cum, off);
+        if (lane >= off) cum += y;
+      }
+      uint32_t before = cum - own;
+#pragma unroll
+      for (int i = 0; i < kPer; ++i) {
+        sh.part[lane * kPer + i] = before;
+        before += c[i];
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const uint64_t xm = x[e] & mask;
+      const bool gt = valid[e] && xm > prefix, eq = valid[e] && xm == prefix;
+      const uint32_t before = sh.part[e * kWaves + wave];
+      const int gt_before = (int)(before & 0xffffu) + __popcll(__ballot(gt) & below);
+      const int eq_before = (int)(before >> 16) + __popcll(__ballot(eq) & below);
+      if (gt || (eq && eq_before < remaining)) {
+        const int pos = gt_before + min(eq_before, remaining);
+        out0[pos] = e * THREADS + tid;
+        if (out1) out1[pos] = e * THREADS + tid;
+      }
+    }
+    return;
+  }
+  bool gt[E], eq[E];
   uint32_t gt_wave = 0, eq_wave = 0, gt_lane = 0, eq_lane = 0;
 #pragma unroll
   for (int e = 0; e < E; ++e) {
