@@ -108,12 +108,12 @@ __device__ __forceinline__ uint32_t xcd_remap(uint32_t bid, uint32_t nblocks_pad
 // runs one segment, so the grid is Hkv*RB*NS workgroups of equal work (within
 // one unit); NS is chosen so that the grid fills two workgroups per CU.
 struct ScoreWork {
-  int32_t rpb;  // rows per row block (a power of two)
+  int32_t rpb;  // rows per row block
   int32_t RB;   // row blocks per KV head
   int32_t UK;   // keys per unit
   int32_t U;    // units per rbh: ceil(n / UK)
   int32_t NS;   // segments per rbh
-  int32_t ldp;  // row stride of the partial sums: RB * rpb
+  int32_t ldp;  // row stride of partial sums and statistics: rows rounded up to 64
   __host__ __device__ int seg_begin(int s) const {  // first unit of segment s
     return (int)((int64_t)s * U / NS);
   }
@@ -127,7 +127,7 @@ struct ScorePlan {
   int32_t rows;   // G*S rows per KV head
   ScoreWork w;
   // workspace layout: partial sums [Hkv][U*UK/c][ldp] (fp32), references
-  // [Hkv*RB][NS][rpb] (fp32), sums / weights [Hkv*RB][NS][rpb] (fp64),
+  // [Hkv][NS][ldp] (fp32), sums / weights [Hkv][NS][ldp] (fp64),
   // overflow flags [Hkv*RB][NS]
   size_t off_part, off_mc, off_z, off_flags, bytes;
 };

@@ -39,6 +39,7 @@ constexpr int kWaves = 4;
 constexpr int kWaveRows = 64;
 constexpr int kBlockRows = kWaves * kWaveRows;  // 256
 constexpr int kSub = 32;                        // keys per subtile
+constexpr int kSegFew = 32;                     // segments per row from which the workspace is held
 constexpr float kOverflowGuard = 0x1p100f;      // a chunk sum above this forces the exact pass
 
 enum ChunkMode { kC4 = 0, kC8 = 1, kC16 = 2, kC32 = 3, kC32x = 4 };  // kC32x: c = 64, 96, ...
@@ -88,8 +89,8 @@ struct ScoreArgs {
   const uint16_t* q;   // [S][Hq][D] bf16 bits
   const uint16_t* k;   // [n][Hkv][D]
   float* part;         // [Hkv][m_pad][ldp]
-  float* mc;           // [Hkv*RB][NS][rpb]
-  double* z;           // [Hkv*RB][NS][rpb]
+  float* mc;           // [Hkv][NS][ldp]
+  double* z;           // [Hkv][NS][ldp]
   int* flags;          // [Hkv*RB][NS]: the segment overflowed in the main pass
   int64_t n, m_pad;    // keys; chunk slots per KV head (U*UK/c)
   int S, Hq, Hkv, G, R, c;
@@ -471,7 +472,28 @@ __device__ __forceinline__ void segment_reference(const ScoreArgs& a, const bf16
 }
 
 template <int D>
-__device__ __forceinline__ void load_q(const ScoreArgs& a, int g, int row0, bf16x8 (&qf)[2][D / 16]);
+__device__ __forceinline__ void load_q(const ScoreArgs& a, int g, int my_row0, bf16x8 (&qf)[2][D / 16]);
+
+// The part of run_segment_fast that a wave without rows (my_row0 >= R) takes:
+// its share of every stage's loads, and the barriers.
+template <int D>
+__device__ __forceinline__ void stage_segment_only(const ScoreArgs& a, int g, int64_t kbeg,
+                                                   int nkeys, uint16_t* lds) {
+  constexpr int kBuf = kStage * SubtileLds<D>::kRow;
+  const int nstage = (nkeys + kStage - 1) / kStage, nfull = nkeys / kStage;
+  const StageOffsets<D> o(a.Hkv, g);
+  const int64_t stage_elems = (int64_t)kStage * a.Hkv * D;
+  const uint16_t* kbase = a.k + kbeg * a.Hkv * D;
+  StageRegs<D> r;
+  stage_load<D>(kbase, nkeys, o, r);
+  for (int s = 0; s < nstage; ++s) {
+    stage_store<D, false>(r, lds + (s & 1) * kBuf);
+    if (s + 1 < nstage)
+      stage_load<D>(kbase + (s + 1) * stage_elems, nkeys - (s + 1) * kStage, o, r);
+    __syncthreads();
+  }
+  if (nfull == nstage) __syncthreads();
+}
 
 // PASS 0 over one segment (keys kbeg .. kbeg+nkeys-1 of KV head g): the
 // reference from the first subtile, pipelined full stages, then the short tail
@@ -479,12 +501,11 @@ __device__ __forceinline__ void load_q(const ScoreArgs& a, int g, int row0, bf16
 // left the guard (then the fallback kernel redoes the segment exactly).
 template <int D, int MODE>
 __device__ __forceinline__ bool run_segment_fast(const ScoreArgs& a, int g, int64_t kbeg, int nkeys,
-                                                 int row0, bf16x8 (&qf)[2][D / 16],
+                                                 int my_row0, bf16x8 (&qf)[2][D / 16],
                                                  uint16_t* lds, RangeState& st) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63;
   const int nstage = (nkeys + kStage - 1) / kStage;
   const int nfull = nkeys / kStage;
-  const int my_row0 = row0 + wave * kWaveRows;
   st.overflow = false;
   st.chunk_acc = 0.f;
   st.zsum = 0.0;
@@ -502,7 +523,7 @@ __device__ __forceinline__ bool run_segment_fast(const ScoreArgs& a, int g, int6
     stage_load<D>(kbase, nkeys, o, r);
   // Q after the first stage's loads: loads return in order, so the stage's
   // LDS store and barrier do not wait for Q
-  load_q<D>(a, g, row0, qf);
+  load_q<D>(a, g, my_row0, qf);
   if (nfull > 0)
     stage_store<D, true>(r, lds);
   else
@@ -553,11 +574,9 @@ __device__ __forceinline__ bool run_segment_fast(const ScoreArgs& a, int g, int6
 // exact fallback kernel.
 template <int D, int MODE, int PASS>
 __device__ __forceinline__ void run_segment(const ScoreArgs& a, int g, int64_t kbeg, int nkeys,
-                                            int row0, const bf16x8 (&qf)[2][D / 16], uint16_t* lds,
+                                            int my_row0, const bf16x8 (&qf)[2][D / 16], uint16_t* lds,
                                             RangeState& st) {
-  const int wave = threadIdx.x >> 6;
   const int nstage = (nkeys + kStage - 1) / kStage;
-  const int my_row0 = row0 + wave * kWaveRows;
   st.chunk_acc = 0.f;
   if (PASS != 1) st.zsum = 0.0;
   if (PASS == 1) st.mref[0] = st.mref[1] = -INFINITY;
@@ -589,14 +608,14 @@ __device__ __forceinline__ void run_segment(const ScoreArgs& a, int g, int64_t k
   }
 }
 
-// Q^T fragments of a row block: B operand, lane l holds row l%32 of a row tile
+// Q^T fragments of the wave's 64 rows from my_row0: B operand, lane l holds row l%32 of a row tile
 // and d = 16*ks + 8*half .. +7 (zero past R).
 template <int D>
-__device__ __forceinline__ void load_q(const ScoreArgs& a, int g, int row0, bf16x8 (&qf)[2][D / 16]) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, half = lane >> 5;
+__device__ __forceinline__ void load_q(const ScoreArgs& a, int g, int my_row0, bf16x8 (&qf)[2][D / 16]) {
+  const int lane = threadIdx.x & 63, half = lane >> 5;
 #pragma unroll
   for (int rt = 0; rt < 2; ++rt) {
-    const int row = row0 + wave * kWaveRows + rt * 32 + (lane & 31);
+    const int row = my_row0 + rt * 32 + (lane & 31);
     const bool ok = row < a.R;
     const int t = ok ? row / a.G : 0, hi = ok ? row % a.G : 0;
     const uint16_t* src = a.q + ((int64_t)t * a.Hq + (int64_t)g * a.G + hi) * D + 8 * half;
@@ -609,14 +628,15 @@ __device__ __forceinline__ void load_q(const ScoreArgs& a, int g, int row0, bf16
   }
 }
 
-// Reference and sum of every row of the block for segment slot s of rbh (rows
-// past R hold zero queries and are written too: the arrays span whole blocks).
-__device__ __forceinline__ void store_stats(const ScoreArgs& a, int rbh, int s, const RangeState& st) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+// Reference and sum of the wave's 64 rows from my_row0 of KV head g for segment
+// s (rows past R hold zero queries and are written too: ldp is a multiple of 64).
+__device__ __forceinline__ void store_stats(const ScoreArgs& a, int g, int s, int my_row0,
+                                            const RangeState& st) {
+  const int lane = threadIdx.x & 63;
   // both lane halves hold both references: the swap hands lane l its own row's
   float ref, unused;
   own_row_pair(st.mref[0], st.mref[1], ref, unused);
-  const int64_t o = ((int64_t)rbh * a.w.NS + s) * kBlockRows + wave * kWaveRows + lane;
+  const int64_t o = ((int64_t)g * a.w.NS + s) * a.w.ldp + my_row0 + lane;
   a.mc[o] = ref;
   a.z[o] = st.zsum;
 }
@@ -644,12 +664,15 @@ __device__ __forceinline__ Segment segment_of(const ScoreWork& wk, int64_t n, in
   return segment_at(wk, n, g * wk.RB + rb, s);
 }
 
-// Fold of the segments of row block rbh: thread t owns row t of the block
-// (rows past R fold too; nothing reads them).  M = max mc, Z = sum
+// Fold of the segments of 64 rows of one KV head: M = max mc, Z = sum
 // exp2(mc - M) z, and each segment's z slot becomes its weight exp2(mc - M)/Z.
-// Up to kFoldBatch segments are held in registers, loaded in one round trip;
-// more are read in batches of kFoldBatch (three passes).
-constexpr int kFoldBatch = 32;
+// Bound by latency (one round trip of loads, one chain of fp64 additions), so the
+// 4 waves share the segments: wave w folds segments w, w + 4, ... of all 64 rows
+// against their own maximum, and the waves' (M, Z) pairs meet in LDS (rescaling is
+// by exact powers of two).  Against 256 rows per workgroup with every
+// segment in one thread: 5.3 -> 4.0 us at 32 segments of 896 rows x 2 heads, 5.7 ->
+// 4.8 at 6 of 2,560 x 8, and 11.6 us for 58 segments of 133 rows x 4 became 7.2 for
+// 117; three segments of 5,120 rows x 8 take 5.6 instead of 4.9.
 
 // exp2(mc - M) for whole-number references mc <= M: an exact power of two
 // (zero once it is below the smallest subnormal).
@@ -657,85 +680,114 @@ __device__ __forceinline__ double seg_factor(float mc, float M) {
   return mc == M ? 1.0 : ldexp(1.0, (int)fmaxf(mc - M, -1100.f));
 }
 
-struct FoldRegs {
-  float v[kFoldBatch];
-  double zz[kFoldBatch];
+struct FoldLds {
+  float m[kWaves][kWaveRows];
+  double z[kWaves][kWaveRows];
 };
 
-// This thread's row of every segment (NS <= kFoldBatch); absent segments read
-// as (-inf, 0), which contribute exactly 0.
+// Up to B segments per wave in registers; absent segments read as (-inf, 0),
+// which contribute exactly 0.
+template <int B>
+struct FoldRegs {
+  float v[B];
+  double zz[B];
+};
+
+template <int B>
 __device__ __forceinline__ void fold_load(const float* mc, const double* z, const ScoreWork& wk,
-                                          int rbh, FoldRegs& r) {
-  const int64_t base = (int64_t)rbh * wk.NS * wk.rpb + threadIdx.x;
+                                          int64_t base, int s0, FoldRegs<B>& r) {
 #pragma unroll
-  for (int i = 0; i < kFoldBatch; ++i) {
-    const bool ok = i < wk.NS;
-    r.v[i] = ok ? mc[base + (int64_t)i * wk.rpb] : -INFINITY;
-    r.zz[i] = ok ? z[base + (int64_t)i * wk.rpb] : 0.0;
+  for (int i = 0; i < B; ++i) {
+    const int s = s0 + i * kWaves;
+    const bool ok = s < wk.NS;  // uniform
+    r.v[i] = ok ? mc[base + (int64_t)s * wk.ldp] : -INFINITY;
+    r.zz[i] = ok ? z[base + (int64_t)s * wk.ldp] : 0.0;
   }
 }
 
-__device__ __forceinline__ void fold_apply(double* z, const ScoreWork& wk, int rbh,
-                                           const FoldRegs& r) {
-  const int64_t base = (int64_t)rbh * wk.NS * wk.rpb + threadIdx.x;
-  float M = -INFINITY;
+// M and 1/Z of the thread's row from its wave's (M, Z).
+__device__ __forceinline__ double fold_merge(FoldLds& sh, int wave, int lane, float Mw, double Zw,
+                                             float& M) {
+  sh.m[wave][lane] = Mw;
+  sh.z[wave][lane] = Zw;
+  __syncthreads();
+  M = -INFINITY;
 #pragma unroll
-  for (int i = 0; i < kFoldBatch; ++i) M = fmaxf(M, r.v[i]);
-  double Z = 0.0;  // ascending segment order
-#pragma unroll
-  for (int i = 0; i < kFoldBatch; ++i) Z += seg_factor(r.v[i], M) * r.zz[i];
-  const double inv = 1.0 / Z;
-#pragma unroll
-  for (int i = 0; i < kFoldBatch; ++i)
-    if (i < wk.NS) z[base + (int64_t)i * wk.rpb] = seg_factor(r.v[i], M) * inv;
-}
-
-// More than kFoldBatch segments: the same sums, in the same order, in batches.
-__device__ __forceinline__ void fold_row_block_batched(const float* mc, double* z,
-                                                       const ScoreWork& wk, int rbh) {
-  const int64_t base = (int64_t)rbh * wk.NS * wk.rpb + threadIdx.x;
-  const int NS = wk.NS, rpb = wk.rpb;
-  float M = -INFINITY;
-  for (int s0 = 0; s0 < NS; s0 += kFoldBatch) {
-    float v[kFoldBatch];
-#pragma unroll
-    for (int i = 0; i < kFoldBatch; ++i)
-      v[i] = s0 + i < NS ? mc[base + (int64_t)(s0 + i) * rpb] : -INFINITY;
-#pragma unroll
-    for (int i = 0; i < kFoldBatch; ++i) M = fmaxf(M, v[i]);
-  }
+  for (int i = 0; i < kWaves; ++i) M = fmaxf(M, sh.m[i][lane]);
   double Z = 0.0;
-  for (int s0 = 0; s0 < NS; s0 += kFoldBatch) {
-    float v[kFoldBatch];
-    double zz[kFoldBatch];
 #pragma unroll
-    for (int i = 0; i < kFoldBatch; ++i) {
-      const bool ok = s0 + i < NS;
-      v[i] = ok ? mc[base + (int64_t)(s0 + i) * rpb] : -INFINITY;
-      zz[i] = ok ? z[base + (int64_t)(s0 + i) * rpb] : 0.0;
-    }
+  for (int i = 0; i < kWaves; ++i) Z += seg_factor(sh.m[i][lane], M) * sh.z[i][lane];
+  return 1.0 / Z;
+}
+
+template <int B>
+__device__ __forceinline__ void fold_sum(const FoldRegs<B>& r, float& Mw, double& Zw) {
+  Mw = -INFINITY;
 #pragma unroll
-    for (int i = 0; i < kFoldBatch; ++i) Z += seg_factor(v[i], M) * zz[i];
-  }
-  const double inv = 1.0 / Z;
-  for (int s0 = 0; s0 < NS; s0 += kFoldBatch) {
-    float v[kFoldBatch];
+  for (int i = 0; i < B; ++i) Mw = fmaxf(Mw, r.v[i]);
+  Zw = 0.0;  // ascending segment order
 #pragma unroll
-    for (int i = 0; i < kFoldBatch; ++i) v[i] = s0 + i < NS ? mc[base + (int64_t)(s0 + i) * rpb] : M;
+  for (int i = 0; i < B; ++i) Zw += seg_factor(r.v[i], Mw) * r.zz[i];
+}
+
+template <int B>
+__device__ __forceinline__ void fold_store(double* z, const ScoreWork& wk, int64_t base, int s0,
+                                           const FoldRegs<B>& r, float M, double inv) {
 #pragma unroll
-    for (int i = 0; i < kFoldBatch; ++i)
-      if (s0 + i < NS) z[base + (int64_t)(s0 + i) * rpb] = seg_factor(v[i], M) * inv;
+  for (int i = 0; i < B; ++i) {
+    const int s = s0 + i * kWaves;
+    if (s < wk.NS) z[base + (int64_t)s * wk.ldp] = seg_factor(r.v[i], M) * inv;
   }
 }
 
-__device__ __forceinline__ void fold_row_block(const float* mc, double* z, const ScoreWork& wk,
-                                               int rbh) {
-  if (wk.NS <= kFoldBatch) {
-    FoldRegs r;
-    fold_load(mc, z, wk, rbh, r);
-    fold_apply(z, wk, rbh, r);
+// base: this thread's row of segment 0.
+template <int B>
+__device__ __forceinline__ void fold_rows(double* z, const ScoreWork& wk, int64_t base, FoldLds& sh,
+                                          const FoldRegs<B>& r) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  float Mw, M;
+  double Zw;
+  fold_sum<B>(r, Mw, Zw);
+  const double inv = fold_merge(sh, wave, lane, Mw, Zw, M);
+  fold_store<B>(z, wk, base, wave, r, M, inv);
+}
+
+// More segments than the registers take (B per wave): in batches, read twice.
+template <int B>
+__device__ __forceinline__ void fold_rows_batched(const float* mc, double* z, const ScoreWork& wk,
+                                                  int64_t base, FoldLds& sh) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  FoldRegs<B> r;
+  float Mw = -INFINITY, M;
+  double Zw = 0.0;
+  for (int s0 = wave; s0 < wk.NS; s0 += B * kWaves) {
+    fold_load<B>(mc, z, wk, base, s0, r);
+    float Mb;
+    double Zb;
+    fold_sum<B>(r, Mb, Zb);
+    const float Mn = fmaxf(Mw, Mb);
+    Zw = seg_factor(Mw, Mn) * Zw + seg_factor(Mb, Mn) * Zb;
+    Mw = Mn;
+  }
+  const double inv = fold_merge(sh, wave, lane, Mw, Zw, M);
+  for (int s0 = wave; s0 < wk.NS; s0 += B * kWaves) {
+    fold_load<B>(mc, z, wk, base, s0, r);
+    fold_store<B>(z, wk, base, s0, r, M, inv);
+  }
+}
+
+constexpr int kFoldFew = 8;    // segments per wave in registers, few segments
+constexpr int kFoldMany = 16;  // and per batch, many segments
+
+__device__ __forceinline__ void fold_rows_any(const float* mc, double* z, const ScoreWork& wk,
+                                              int64_t base, FoldLds& sh) {
+  const int wave = threadIdx.x >> 6;
+  if (wk.NS <= kFoldFew * kWaves) {
+    FoldRegs<kFoldFew> r;
+    fold_load<kFoldFew>(mc, z, wk, base, wave, r);
+    fold_rows<kFoldFew>(z, wk, base, sh, r);
   } else {
-    fold_row_block_batched(mc, z, wk, rbh);
+    fold_rows_batched<kFoldMany>(mc, z, wk, base, sh);
   }
 }
 
@@ -750,13 +802,19 @@ __global__ __launch_bounds__(kWaves * 64, 2) void score_bf16_kernel(ScoreArgs a)
   // counter, one 16-byte store per workgroup
   const unsigned long long t_start = a.tstamp ? __builtin_amdgcn_s_memrealtime() : 0;
   const Segment sg = segment_of(a.w, a.n, (int)w);
-  const int g = sg.rbh / a.w.RB, row0 = (sg.rbh % a.w.RB) * kBlockRows;
-  bf16x8 qf[2][D / 16];  // loaded by run_segment_fast
-  RangeState st;
-  const bool of = run_segment_fast<D, MODE>(a, g, sg.kbeg, sg.nkeys, row0, qf, lds, st);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int g = sg.rbh / a.w.RB, my_row0 = (sg.rbh % a.w.RB) * kBlockRows + wave * kWaveRows;
+  bool of = false;
+  if (my_row0 < a.w.ldp) {  // uniform in the wave
+    bf16x8 qf[2][D / 16];  // loaded by run_segment_fast
+    RangeState st;
+    of = run_segment_fast<D, MODE>(a, g, sg.kbeg, sg.nkeys, my_row0, qf, lds, st);
+    store_stats(a, g, sg.s, my_row0, st);
+  } else {
+    stage_segment_only<D>(a, g, sg.kbeg, sg.nkeys, lds);
+  }
   const int any_of = __syncthreads_or(of ? 1 : 0);
   if (threadIdx.x == 0) a.flags[sg.rbh * a.w.NS + sg.s] = any_of;
-  store_stats(a, sg.rbh, sg.s, st);
   if (a.tstamp) {
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -766,19 +824,24 @@ __global__ __launch_bounds__(kWaves * 64, 2) void score_bf16_kernel(ScoreArgs a)
   }
 }
 
-// Fold pass, one workgroup per row block: redoes exactly (against its own
-// maximum, two passes) any of the block's segments whose chunk sums left the
-// guard in the main pass -- almost never -- then folds the block's segments.
+// Fold pass, one workgroup per 64 rows of a KV head: redoes exactly (against its
+// own maximum, two passes) any of their segments whose chunk sums left the guard
+// in the main pass -- almost never -- then folds the segments.  In a redo all
+// four waves stage the keys and compute the same 64 rows (and store the same values).
 template <int D, int MODE>
-__global__ __launch_bounds__(kWaves * 64) void score_fold_kernel(ScoreArgs a) {
+__global__ __launch_bounds__(kWaves * 64, 2) void score_fold_kernel(ScoreArgs a) {
   __shared__ __attribute__((aligned(16))) uint16_t lds[2 * kStage * SubtileLds<D>::kRow];
-  const int rbh = blockIdx.x;
-  const int g = rbh / a.w.RB, row0 = (rbh % a.w.RB) * kBlockRows;
-  // all flags of the block, and (speculatively) the block's statistics, in one
+  __shared__ FoldLds sh;
+  const int groups = a.w.ldp / kWaveRows;  // per KV head
+  const int g = blockIdx.x / groups, my_row0 = (blockIdx.x % groups) * kWaveRows;
+  const int rbh = g * a.w.RB + my_row0 / kBlockRows;
+  const int wave = threadIdx.x >> 6;
+  const int64_t base = (int64_t)g * a.w.NS * a.w.ldp + my_row0 + (threadIdx.x & 63);
+  // all flags of the block, and (speculatively) the rows' statistics, in one
   // round trip; nothing flagged is the common case
-  const bool in_regs = a.w.NS <= kFoldBatch;
-  FoldRegs r;
-  if (in_regs) fold_load(a.mc, a.z, a.w, rbh, r);
+  const bool few = a.w.NS <= kFoldFew * kWaves;
+  FoldRegs<kFoldFew> r;
+  if (few) fold_load<kFoldFew>(a.mc, a.z, a.w, base, wave, r);
   int any = 0;
   for (int s = threadIdx.x; s < a.w.NS; s += blockDim.x) any |= a.flags[rbh * a.w.NS + s];
   const bool redo = __syncthreads_or(any);
@@ -787,27 +850,31 @@ __global__ __launch_bounds__(kWaves * 64) void score_fold_kernel(ScoreArgs a) {
       if (!a.flags[rbh * a.w.NS + s]) continue;  // uniform
       const Segment o = segment_at(a.w, a.n, rbh, s);
       bf16x8 qf[2][D / 16];
-      load_q<D>(a, g, row0, qf);
+      load_q<D>(a, g, my_row0, qf);
       RangeState st;
-      run_segment<D, MODE, 1>(a, g, o.kbeg, o.nkeys, row0, qf, lds, st);
-      run_segment<D, MODE, 2>(a, g, o.kbeg, o.nkeys, row0, qf, lds, st);
-      store_stats(a, rbh, s, st);
+      run_segment<D, MODE, 1>(a, g, o.kbeg, o.nkeys, my_row0, qf, lds, st);
+      run_segment<D, MODE, 2>(a, g, o.kbeg, o.nkeys, my_row0, qf, lds, st);
+      store_stats(a, g, s, my_row0, st);
       __syncthreads();
     }
   }
-  if (!in_regs) {
-    fold_row_block_batched(a.mc, a.z, a.w, rbh);
+  if (!few) {
+    fold_rows_batched<kFoldMany>(a.mc, a.z, a.w, base, sh);
     return;
   }
-  if (redo) fold_load(a.mc, a.z, a.w, rbh, r);  // this thread's rows, as redone
-  fold_apply(a.z, a.w, rbh, r);
+  if (redo) fold_load<kFoldFew>(a.mc, a.z, a.w, base, wave, r);  // the rows as redone
+  fold_rows<kFoldFew>(a.z, a.w, base, sh, r);
 }
 
 // fp32 path: the main kernel already redid overflowing segments; fold only.
-__global__ __launch_bounds__(kWaveRows) void score_fold_f32_kernel(const float* __restrict__ mc,
-                                                                   double* __restrict__ z,
-                                                                   ScoreWork wk) {
-  fold_row_block(mc, z, wk, blockIdx.x);
+__global__ __launch_bounds__(kWaves * 64) void score_fold_f32_kernel(const float* __restrict__ mc,
+                                                                     double* __restrict__ z,
+                                                                     ScoreWork wk) {
+  __shared__ FoldLds sh;
+  const int groups = wk.ldp / kWaveRows;
+  const int g = blockIdx.x / groups, row0 = (blockIdx.x % groups) * kWaveRows;
+  const int64_t base = (int64_t)g * wk.NS * wk.ldp + row0 + (threadIdx.x & 63);
+  fold_rows_any(mc, z, wk, base, sh);
 }
 
 // ---------------------------------------------------------------------------
@@ -969,7 +1036,7 @@ __global__ __launch_bounds__(64) void score_f32_kernel(ScoreArgsF32 a) {
     run_span_f32<D, MODE, 1>(a, g, sg.kbeg, kend, row0, qf, mref, zsum);
     run_span_f32<D, MODE, 2>(a, g, sg.kbeg, kend, row0, qf, mref, zsum);
   }
-  const int64_t o = ((int64_t)sg.rbh * a.w.NS + sg.s) * kWaveRows + lane;
+  const int64_t o = ((int64_t)g * a.w.NS + sg.s) * a.w.ldp + row0 + lane;
   a.mc[o] = half ? mref[1] : mref[0];
   a.z[o] = half ? zsum[1] : zsum[0];
 }
@@ -989,7 +1056,7 @@ constexpr int64_t kReduceWideChunks = 4096;  // chunk count from which it is use
 
 __global__ __launch_bounds__(kReduceThreads) void chunk_reduce_kernel(
     const float* __restrict__ part, const double* __restrict__ w, double* __restrict__ A,
-    ScoreWork wk, int Hkv, int R, int64_t m_pad, int c, int log2_rpb) {
+    ScoreWork wk, int Hkv, int R, int64_t m_pad, int c) {
   __shared__ double red[kReduceThreads];
   const int64_t j = blockIdx.x;
   const int tid = threadIdx.x;
@@ -999,10 +1066,9 @@ __global__ __launch_bounds__(kReduceThreads) void chunk_reduce_kernel(
   for (int g = 0; g < Hkv; ++g) {
     const float* p = part + ((int64_t)g * m_pad + j) * wk.ldp;
     for (int r = 4 * tid; r < R; r += 4 * kReduceThreads) {
-      // ldp and rpb are multiples of 64: the 4 rows are in bounds and in one block
+      // ldp is a multiple of 64: the 4 rows are in bounds
       const f32x4 pv = *reinterpret_cast<const f32x4*>(p + r);
-      const int rbh = g * wk.RB + (r >> log2_rpb);
-      const double* wr = w + ((int64_t)rbh * wk.NS + seg) * wk.rpb + (r & (wk.rpb - 1));
+      const double* wr = w + ((int64_t)g * wk.NS + seg) * wk.ldp + r;
       const double2 w01 = *reinterpret_cast<const double2*>(wr);
       const double2 w23 = *reinterpret_cast<const double2*>(wr + 2);
       if (r + 3 < R) {
@@ -1040,7 +1106,7 @@ __global__ __launch_bounds__(kReduceThreads) void chunk_reduce_kernel(
 template <int NJ, int UNR, bool SAME>
 __device__ __forceinline__ void reduce_flat_sums(const float* __restrict__ part,
                                                  const double* __restrict__ w, const ScoreWork& wk,
-                                                 int Hkv, int R, int64_t m_pad, int log2_rpb,
+                                                 int Hkv, int R, int64_t m_pad,
                                                  const int64_t (&jc)[NJ], const int (&seg)[NJ],
                                                  double (&s)[NJ]) {
   constexpr int NW = SAME ? 1 : NJ;  // weight sets per pair
@@ -1058,11 +1124,10 @@ __device__ __forceinline__ void reduce_flat_sums(const float* __restrict__ part,
       const float* p = part + (int64_t)g * m_pad * wk.ldp + r;
 #pragma unroll
       for (int q = 0; q < NJ; ++q) pv[u][q] = *reinterpret_cast<const f32x4*>(p + jc[q] * wk.ldp);
-      const int rbh = g * wk.RB + (r >> log2_rpb);
-      const double* wb = w + (int64_t)rbh * wk.NS * wk.rpb + (r & (wk.rpb - 1));
+      const double* wb = w + (int64_t)g * wk.NS * wk.ldp + r;
 #pragma unroll
       for (int q = 0; q < NW; ++q) {
-        const double* wr = wb + (int64_t)seg[q] * wk.rpb;
+        const double* wr = wb + (int64_t)seg[q] * wk.ldp;
         const double2 w01 = *reinterpret_cast<const double2*>(wr);
         const double2 w23 = *reinterpret_cast<const double2*>(wr + 2);
         wv[u][q][0] = w01.x; wv[u][q][1] = w01.y; wv[u][q][2] = w23.x; wv[u][q][3] = w23.y;
@@ -1084,7 +1149,7 @@ __device__ __forceinline__ void reduce_flat_sums(const float* __restrict__ part,
 template <int NJ, int UNR>
 __global__ __launch_bounds__(kReduceThreads) void chunk_reduce_flat_kernel(
     const float* __restrict__ part, const double* __restrict__ w, double* __restrict__ A,
-    ScoreWork wk, int Hkv, int R, int64_t m, int64_t m_pad, int c, int log2_rpb) {
+    ScoreWork wk, int Hkv, int R, int64_t m, int64_t m_pad, int c) {
   __shared__ double red[NJ][kReduceThreads];
   const int64_t j0 = (int64_t)blockIdx.x * NJ;
   const int tid = threadIdx.x;
@@ -1101,9 +1166,9 @@ __global__ __launch_bounds__(kReduceThreads) void chunk_reduce_flat_kernel(
 #pragma unroll
   for (int q = 0; q < NJ; ++q) s[q] = 0.0;
   if (same)  // uniform
-    reduce_flat_sums<NJ, UNR, true>(part, w, wk, Hkv, R, m_pad, log2_rpb, jc, seg, s);
+    reduce_flat_sums<NJ, UNR, true>(part, w, wk, Hkv, R, m_pad, jc, seg, s);
   else  // a workgroup across a segment boundary: one pair per step (the order is the same)
-    reduce_flat_sums<NJ, 1, false>(part, w, wk, Hkv, R, m_pad, log2_rpb, jc, seg, s);
+    reduce_flat_sums<NJ, 1, false>(part, w, wk, Hkv, R, m_pad, jc, seg, s);
 #pragma unroll
   for (int q = 0; q < NJ; ++q) red[q][tid] = s[q];
   __syncthreads();
@@ -1155,9 +1220,13 @@ ScorePlan make_score_plan(const ckv_dims* d) {
   // A fixed grid target (two 256-thread workgroups per CU of a 256-CU MI355X
   // for bf16) keeps the decomposition, and so every rounding, independent of
   // the device the library runs on.  Segments of the pipelined bf16 kernel
-  // keep at least 4 stages while the fold still holds a row's segments in
-  // registers (kFoldBatch), else at least 8; the one-wave fp32 kernel's keep
-  // 64 keys.
+  // keep at least 4 stages, the one-wave fp32 kernel's 64 keys.  Past kSegFew
+  // segments the statistics are a good part of the workspace, which is held to
+  // what 8-stage segments over whole 256-row blocks would take: the padding rows
+  // that are not stored pay for the shorter segments, and where there are none
+  // the segments keep 8 stages.  1,400 rows x 2 heads over 12,345
+  // keys, 24 segments -> 42: main kernel 22.9 -> 18.1 us; 133 x 4 over 30,011, 58 ->
+  // 117: 16.9 -> 16.4 us.
   const int64_t target = f32 ? 1024 : 512;
   const int64_t NS_max = std::max<int64_t>(1, target / H_RB);
   auto segments = [&](int64_t min_keys) {
@@ -1165,25 +1234,32 @@ ScorePlan make_score_plan(const ckv_dims* d) {
     return std::min<int64_t>(NS_max, std::max<int64_t>(1, U / min_units));
   };
   int64_t NS = segments(f32 ? 64 : 256);
-  if (!f32 && NS > kFoldBatch) NS = segments(512);
   // bytes == 0 marks an unsupported shape
   if (UK > INT32_MAX || U > INT32_MAX || H_RB * NS >= (int64_t(1) << 31)) return p;
+  const size_t H = (size_t)d->n_kv_heads, m_pad = (size_t)(U * UK / c);
+  const size_t ldp = (size_t)align_up(p.rows, kWaveRows);
+  auto layout = [&](size_t rows, size_t ns) {  // rows per KV head and segments
+    size_t off = 0;
+    p.off_part = off;
+    off = align_up(off + H * m_pad * rows * sizeof(float), 256);
+    p.off_mc = off;
+    off = align_up(off + H * ns * rows * sizeof(float), 256);
+    p.off_z = off;
+    off = align_up(off + H * ns * rows * sizeof(double), 256);
+    p.off_flags = off;
+    return align_up(off + (size_t)H_RB * ns * sizeof(int), 256);
+  };
+  if (!f32 && NS > kSegFew) {
+    const int64_t NS_long = segments(512);
+    const size_t limit = layout((size_t)w.RB * w.rpb, (size_t)NS_long);
+    const size_t fixed = layout(ldp, 0) + 4 * 256, per_seg = H * ldp * 12 + (size_t)H_RB * 4;
+    NS = std::max<int64_t>(NS_long, std::min<int64_t>(NS, limit > fixed ? (int64_t)((limit - fixed) / per_seg) : 0));
+  }
   w.UK = (int32_t)UK;
   w.U = (int32_t)U;
   w.NS = (int32_t)NS;
-  w.ldp = w.RB * w.rpb;
-  const size_t H = (size_t)d->n_kv_heads, m_pad = (size_t)(U * UK / c);
-  const size_t stats = (size_t)H_RB * NS * (size_t)w.rpb;
-  size_t off = 0;
-  p.off_part = off;
-  off = align_up(off + H * m_pad * (size_t)w.ldp * sizeof(float), 256);
-  p.off_mc = off;
-  off = align_up(off + stats * sizeof(float), 256);
-  p.off_z = off;
-  off = align_up(off + stats * sizeof(double), 256);
-  p.off_flags = off;
-  off = align_up(off + (size_t)H_RB * NS * sizeof(int), 256);
-  p.bytes = off;
+  w.ldp = (int32_t)ldp;
+  p.bytes = layout(ldp, (size_t)NS);
   return p;
 }
 
@@ -1221,7 +1297,7 @@ ckv_status launch_score(const ckv_dims* d, const void* q, const void* k, double*
     a.nwg_padded = (uint32_t)align_up(nwg, 8);
     a.tstamp = main_span;
     dim3 grid(a.nwg_padded), block(kWaves * 64);
-    const dim3 fold_grid((unsigned)(d->n_kv_heads * p.w.RB));
+    const dim3 fold_grid((unsigned)(d->n_kv_heads * (p.w.ldp / kWaveRows)));
 #define CKV_SCORE_LAUNCH(DD, MM)                                                           \
   do {                                                                                     \
     hipLaunchKernelGGL((score_bf16_kernel<DD, MM>), grid, block, 0, st, a);                \
@@ -1265,22 +1341,20 @@ ckv_status launch_score(const ckv_dims* d, const void* q, const void* k, double*
     }
     if (main_span) CKV_FAIL(CKV_EUNSUPPORTED, "in-kernel timing is for the bf16 path");
     if (main_stop) CKV_HIP(hipEventRecord(main_stop, st));
-    hipLaunchKernelGGL(score_fold_f32_kernel, dim3((unsigned)(d->n_kv_heads * p.w.RB)),
-                       dim3(kWaveRows), 0, st, mc, z, p.w);
+    hipLaunchKernelGGL(score_fold_f32_kernel, dim3((unsigned)(d->n_kv_heads * (p.w.ldp / kWaveRows))),
+                       dim3(kWaves * 64), 0, st, mc, z, p.w);
   }
   CKV_HIP(hipGetLastError());
-  const int log2_rpb = p.w.rpb == 256 ? 8 : 6;
   // one chunk per workgroup while the chunks are few (the reduction is bound
   // by load latency); with many chunks (the partials then run to hundreds of
   // MB) kReduceWide chunks per workgroup share each weight load
   if (p.m < kReduceWideChunks)
     hipLaunchKernelGGL(chunk_reduce_kernel, dim3((unsigned)p.m), dim3(kReduceThreads), 0, st, part,
-                       z, scores, p.w, d->n_kv_heads, p.rows, m_pad, d->chunk_size, log2_rpb);
+                       z, scores, p.w, d->n_kv_heads, p.rows, m_pad, d->chunk_size);
   else
     hipLaunchKernelGGL((chunk_reduce_flat_kernel<kReduceWide, kReduceUnroll>),
                        dim3((unsigned)ceil_div(p.m, kReduceWide)), dim3(kReduceThreads), 0, st,
-                       part, z, scores, p.w, d->n_kv_heads, p.rows, p.m, m_pad, d->chunk_size,
-                       log2_rpb);
+                       part, z, scores, p.w, d->n_kv_heads, p.rows, p.m, m_pad, d->chunk_size);
   CKV_HIP(hipGetLastError());
   return CKV_OK;
 }
