@@ -880,7 +880,15 @@ __global__ __launch_bounds__(kWaves * 64) void score_fold_f32_kernel(const float
 // ---------------------------------------------------------------------------
 // fp32 kernel (v_mfma_f32_32x32x2_f32), same structure without LDS staging:
 // K fragments are read straight from global memory (the fp32 workloads are
-// small).  One wave per workgroup, 64 rows.
+// small).
+//
+// Bound by load latency and the chain of a subtile's MFMAs (64 cycles each): a few
+// 32-key subtiles per wave, each behind its loads.  One wave holds 32 rows.
+// A lane loads elements 8j + 4*half .. + 3 of its K and Q rows (j = 0 .. D/8 - 1;
+// D/8 16-byte loads a fragment) and trades with its partner lane for the elements
+// 2i + half that MFMA i takes; a subtile's loads are issued before the previous
+// one is computed.  One wave of 64 rows with 4-byte loads of those elements took
+// 10.4 us for 128 rows over 1,024 keys, this 6.6.
 // ---------------------------------------------------------------------------
 struct ScoreArgsF32 {
   const float* q;
@@ -895,150 +903,147 @@ struct ScoreArgsF32 {
   int nwg;
 };
 
+// f[j] = elements 8j + 4*half .. + 3 becomes elements 8j + 2e + half, e = 0 .. 3.
+__device__ __forceinline__ f32x4 pair_elements(f32x4 f) {
+  auto swap = [](float x, float y, float& lo, float& hi) __attribute__((always_inline)) {
+    auto r = __builtin_amdgcn_permlane32_swap(__float_as_int(x), __float_as_int(y), false, false);
+    lo = __int_as_float(r[0]);
+    hi = __int_as_float(r[1]);
+  };
+  float e0, e1, e2, e3;
+  swap(f[0], f[1], e0, e2);
+  swap(f[2], f[3], e1, e3);
+  return f32x4{e0, e1, e2, e3};
+}
+
+// One wave's 32 rows from row0 (lane l and l^32 hold row l%32).
 template <int D, int MODE, int PASS>
 __device__ bool run_span_f32(const ScoreArgsF32& a, int g, int64_t kbeg, int64_t kend, int row0,
-                             const float (&qf)[2][D / 2], float (&mref)[2], double (&zsum)[2]) {
+                             const f32x4 (&qf)[D / 8], float& mref, double& zsum) {
   const int lane = threadIdx.x & 63, half = lane >> 5;
+  const int row = row0 + (lane & 31);
   const int nsub = (int)((kend - kbeg + kSub - 1) / kSub);
   bool overflow = false;
-  float chunk_acc[2] = {0.f, 0.f};
-  if (PASS != 1) { zsum[0] = 0.0; zsum[1] = 0.0; }
-  if (PASS == 1) { mref[0] = -INFINITY; mref[1] = -INFINITY; }
+  float chunk_acc = 0.f;
+  if (PASS != 1) zsum = 0.0;
+  if (PASS == 1) mref = -INFINITY;
   float* part = a.part + ((int64_t)g * a.m_pad + kbeg / a.c) * a.w.ldp;
+  f32x4 kf[D / 8], kn[D / 8];  // this subtile's fragment and the next one's
+  auto load_k = [&](int s, f32x4 (&f)[D / 8]) __attribute__((always_inline)) {
+    const int64_t mykey = kbeg + (int64_t)s * kSub + (lane & 31);
+    const float* krow = a.k + (min<int64_t>(mykey, a.n - 1) * a.Hkv + g) * D + 4 * half;
+#pragma unroll
+    for (int j = 0; j < D / 8; ++j) f[j] = *reinterpret_cast<const f32x4*>(krow + 8 * j);
+  };
+  load_k(0, kn);
   for (int s = 0; s < nsub; ++s) {
     const int64_t key0 = kbeg + (int64_t)s * kSub;
     const int nvalid = (int)min<int64_t>(kSub, kend - key0);
-    const int64_t mykey = key0 + (lane & 31);
-    const float* krow = a.k + (min<int64_t>(mykey, a.n - 1) * a.Hkv + g) * D;
-    f32x16 acc[2];
 #pragma unroll
-    for (int rt = 0; rt < 2; ++rt)
+    for (int j = 0; j < D / 8; ++j) kf[j] = pair_elements(kn[j]);
+    if (s + 1 < nsub) load_k(s + 1, kn);
+    f32x16 acc;
 #pragma unroll
-      for (int v = 0; v < 16; ++v) acc[rt][v] = 0.f;
+    for (int v = 0; v < 16; ++v) acc[v] = 0.f;
 #pragma unroll
-    for (int ks = 0; ks < D / 2; ++ks) {
-      float kf = krow[2 * ks + half];
-      acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(kf, qf[0][ks], acc[0], 0, 0, 0);
-      acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(kf, qf[1][ks], acc[1], 0, 0, 0);
-    }
+    for (int i = 0; i < D / 2; ++i)
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[i >> 2][i & 3], qf[i >> 2][i & 3], acc, 0, 0, 0);
     if (PASS == 1 || (PASS == 0 && s == 0)) {
-#pragma unroll
-      for (int rt = 0; rt < 2; ++rt) {
-        float mx = -INFINITY;
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          int key = 8 * (v >> 2) + 4 * half + (v & 3);
-          if (key < nvalid) mx = fmaxf(mx, acc[rt][v]);
-        }
-        mx = fmaxf(mx, partner_f(mx));
-        if (PASS == 1)
-          mref[rt] = fmaxf(mref[rt], ceilf(mx * a.c1));
-        else
-          mref[rt] = ceilf(mx * a.c1);
-      }
-    }
-    if (PASS == 1) continue;
-#pragma unroll
-    for (int rt = 0; rt < 2; ++rt) {
-      const float nm = -mref[rt];
+      float mx = -INFINITY;
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
         int key = 8 * (v >> 2) + 4 * half + (v & 3);
-        float e = __builtin_amdgcn_exp2f(fmaf(acc[rt][v], a.c1, nm));
-        acc[rt][v] = key < nvalid ? e : 0.f;
+        if (key < nvalid) mx = fmaxf(mx, acc[v]);
       }
+      mx = fmaxf(mx, partner_f(mx));
+      if (PASS == 1)
+        mref = fmaxf(mref, ceilf(mx * a.c1));
+      else
+        mref = ceilf(mx * a.c1);
+    }
+    if (PASS == 1) continue;
+    const float nm = -mref;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      int key = 8 * (v >> 2) + 4 * half + (v & 3);
+      float e = __builtin_amdgcn_exp2f(fmaf(acc[v], a.c1, nm));
+      acc[v] = key < nvalid ? e : 0.f;
     }
     if constexpr (MODE >= kC32) {
       const int64_t chunk = key0 / a.c;
       const bool closes = ((key0 + kSub) % a.c == 0) || (s == nsub - 1);
-#pragma unroll
-      for (int rt = 0; rt < 2; ++rt) {
-        float sum;
-        chunk_sums<MODE>(acc[rt], &sum);
-        chunk_acc[rt] += sum;
-      }
+      float sum;
+      chunk_sums<MODE>(acc, &sum);
+      chunk_acc += sum;
       if (closes) {
         const int jl = (int)(chunk - kbeg / a.c);
-        const int row = row0 + lane;
-        float mine = half ? chunk_acc[1] : chunk_acc[0];
-        if (row < a.R) part[(int64_t)jl * a.w.ldp + row] = mine;
-#pragma unroll
-        for (int rt = 0; rt < 2; ++rt) {
-          overflow |= !(chunk_acc[rt] <= kOverflowGuard);
-          zsum[rt] += (double)chunk_acc[rt];
-          chunk_acc[rt] = 0.f;
-        }
+        if (half == 0 && row < a.R) part[(int64_t)jl * a.w.ldp + row] = chunk_acc;
+        overflow |= !(chunk_acc <= kOverflowGuard);
+        zsum += (double)chunk_acc;
+        chunk_acc = 0.f;
       }
     } else {
       constexpr int kN = sums_per_lane<MODE>();
       const int jl0 = (int)((key0 - kbeg) / a.c);
+      float sums[kN];
+      chunk_sums<MODE>(acc, sums);
 #pragma unroll
-      for (int rt = 0; rt < 2; ++rt) {
-        float sums[kN];
-        chunk_sums<MODE>(acc[rt], sums);
+      for (int i = 0; i < kN; ++i) {
+        overflow |= !(sums[i] <= kOverflowGuard);
+        zsum += (double)sums[i];
+      }
 #pragma unroll
-        for (int i = 0; i < kN; ++i) {
-          overflow |= !(sums[i] <= kOverflowGuard);
-          zsum[rt] += (double)sums[i];
-        }
-        if constexpr (MODE == kC4) {
-          const int row = row0 + rt * 32 + (lane & 31);
-#pragma unroll
-          for (int i = 0; i < kN; ++i) {
-            int jl = jl0 + 2 * i + half;
-            int key_first = 8 * i + 4 * half;
-            if (row < a.R && key_first < nvalid) part[(int64_t)jl * a.w.ldp + row] = sums[i];
-          }
-        } else if (rt == half) {
-          const int row = row0 + rt * 32 + (lane & 31);
-#pragma unroll
-          for (int i = 0; i < kN; ++i) {
-            int key_first = i * (kSub / kN);
-            if (row < a.R && key_first < nvalid) part[(int64_t)(jl0 + i) * a.w.ldp + row] = sums[i];
-          }
-        }
+      for (int i = 0; i < kN; ++i) {
+        // kC4: each lane half holds its own chunks; else both hold every chunk
+        const int jl = MODE == kC4 ? 2 * i + half : i;
+        const int key_first = MODE == kC4 ? 8 * i + 4 * half : i * (kSub / kN);
+        if ((MODE == kC4 || half == 0) && row < a.R && key_first < nvalid)
+          part[(int64_t)(jl0 + jl) * a.w.ldp + row] = sums[i];
       }
     }
   }
   if constexpr (MODE == kC4) {
-#pragma unroll
-    for (int rt = 0; rt < 2; ++rt) {
-      double o = partner_d(zsum[rt]);
-      zsum[rt] = half ? (o + zsum[rt]) : (zsum[rt] + o);
-    }
+    double o = partner_d(zsum);
+    zsum = half ? (o + zsum) : (zsum + o);
   }
   return overflow;
 }
 
+// Two waves per workgroup, 32 of its 64 rows each.
+constexpr int kF32Waves = 2;
 template <int D, int MODE>
-__global__ __launch_bounds__(64) void score_f32_kernel(ScoreArgsF32 a) {
+__global__ __launch_bounds__(64 * kF32Waves) void score_f32_kernel(ScoreArgsF32 a) {
   const int w = blockIdx.x;
   if (w >= a.nwg) return;
-  const int lane = threadIdx.x & 63, half = lane >> 5;
+  const int lane = threadIdx.x & 63, half = lane >> 5, wave = threadIdx.x >> 6;
   const Segment sg = segment_of(a.w, a.n, w);
-  const int g = sg.rbh / a.w.RB, row0 = (sg.rbh % a.w.RB) * kWaveRows;
-  float qf[2][D / 2];
-#pragma unroll
-  for (int rt = 0; rt < 2; ++rt) {
-    const int row = row0 + rt * 32 + (lane & 31);
+  const int g = sg.rbh / a.w.RB, row0 = (sg.rbh % a.w.RB) * kWaveRows + 32 * wave;
+  f32x4 qf[D / 8];
+  const int row = row0 + (lane & 31);
+  {
     const bool ok = row < a.R;
     const int t = ok ? row / a.G : 0, hi = ok ? row % a.G : 0;
-    const float* src = a.q + ((int64_t)t * a.Hq + (int64_t)g * a.G + hi) * D + half;
+    const float* src = a.q + ((int64_t)t * a.Hq + (int64_t)g * a.G + hi) * D + 4 * half;
 #pragma unroll
-    for (int ks = 0; ks < D / 2; ++ks) qf[rt][ks] = ok ? src[2 * ks] : 0.f;
+    for (int j = 0; j < D / 8; ++j) {
+      const f32x4 v = *reinterpret_cast<const f32x4*>(src + 8 * j);
+      qf[j] = pair_elements(ok ? v : f32x4{0.f, 0.f, 0.f, 0.f});
+    }
   }
-  float mref[2];
-  double zsum[2];
+  float mref;
+  double zsum;
   const int64_t kend = sg.kbeg + sg.nkeys;
   bool of = run_span_f32<D, MODE, 0>(a, g, sg.kbeg, kend, row0, qf, mref, zsum);
-  // one wave: the decision is wave-uniform via a ballot
+  // the decision is the wave's own: a ballot
   if (__any(of)) {
     run_span_f32<D, MODE, 1>(a, g, sg.kbeg, kend, row0, qf, mref, zsum);
     run_span_f32<D, MODE, 2>(a, g, sg.kbeg, kend, row0, qf, mref, zsum);
   }
-  const int64_t o = ((int64_t)g * a.w.NS + sg.s) * a.w.ldp + row0 + lane;
-  a.mc[o] = half ? mref[1] : mref[0];
-  a.z[o] = half ? zsum[1] : zsum[0];
+  if (half == 0) {
+    const int64_t o = ((int64_t)g * a.w.NS + sg.s) * a.w.ldp + row;
+    a.mc[o] = mref;
+    a.z[o] = zsum;
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -1220,7 +1225,7 @@ ScorePlan make_score_plan(const ckv_dims* d) {
   // A fixed grid target (two 256-thread workgroups per CU of a 256-CU MI355X
   // for bf16) keeps the decomposition, and so every rounding, independent of
   // the device the library runs on.  Segments of the pipelined bf16 kernel
-  // keep at least 4 stages, the one-wave fp32 kernel's 64 keys.  Past kSegFew
+  // keep at least 4 stages, the fp32 kernel's 64 keys.  Past kSegFew
   // segments the statistics are a good part of the workspace, which is held to
   // what 8-stage segments over whole 256-row blocks would take: the padding rows
   // that are not stored pay for the shorter segments, and where there are none
@@ -1331,7 +1336,7 @@ ckv_status launch_score(const ckv_dims* d, const void* q, const void* k, double*
     a.S = d->n_suffix; a.Hq = d->n_q_heads; a.Hkv = d->n_kv_heads; a.G = G;
     a.R = p.rows; a.c = d->chunk_size; a.c1 = c1; a.w = p.w;
     a.nwg = (int)nwg;
-    dim3 grid(nwg), block(64);
+    dim3 grid(nwg), block(64 * kF32Waves);
     switch (mode) {
       case kC4: hipLaunchKernelGGL((score_f32_kernel<64, kC4>), grid, block, 0, st, a); break;
       case kC8: hipLaunchKernelGGL((score_f32_kernel<64, kC8>), grid, block, 0, st, a); break;
