@@ -1225,13 +1225,14 @@ ScorePlan make_score_plan(const ckv_dims* d) {
   // A fixed grid target (two 256-thread workgroups per CU of a 256-CU MI355X
   // for bf16) keeps the decomposition, and so every rounding, independent of
   // the device the library runs on.  Segments of the pipelined bf16 kernel
-  // keep at least 4 stages, the fp32 kernel's 64 keys.  Past kSegFew
+  // keep at least 4 stages (but see below), the fp32 kernel's 64 keys.  Past kSegFew
   // segments the statistics are a good part of the workspace, which is held to
   // what 8-stage segments over whole 256-row blocks would take: the padding rows
   // that are not stored pay for the shorter segments, and where there are none
   // the segments keep 8 stages.  1,400 rows x 2 heads over 12,345
   // keys, 24 segments -> 42: main kernel 22.9 -> 18.1 us; 133 x 4 over 30,011, 58 ->
   // 117: 16.9 -> 16.4 us.
+  constexpr int64_t kCus = 256;
   const int64_t target = f32 ? 1024 : 512;
   const int64_t NS_max = std::max<int64_t>(1, target / H_RB);
   auto segments = [&](int64_t min_keys) {
@@ -1239,6 +1240,23 @@ ScorePlan make_score_plan(const ckv_dims* d) {
     return std::min<int64_t>(NS_max, std::max<int64_t>(1, U / min_units));
   };
   int64_t NS = segments(f32 ? 64 : 256);
+  // A launch that leaves half of the CUs or more without a workgroup is bound by the
+  // chain of one segment's stages (about 1 us each): it takes the shortest segments
+  // that still give at most one workgroup per CU and at most the kSegFew segments per
+  // row that the fold holds in registers.  Whole layers, 4-stage segments against
+  // these: 8 workgroups (1,000 keys x 168 rows x 2 heads) 28.3 -> 25.1 us, 64 (2,048 x
+  // 448 x 4) 34.0 -> 31.6, 96 (1,024 x 640 x 8) 36.2 -> 34.8, 128 (1,100 x 1,000 x 8)
+  // 39.8 -> 38.1; scoring alone, 32 (1,200 x 32 x 8) 18.1 -> 14.5.  Past that
+  // the shorter segments cost more than they give: 192 (1,500 x 1,000 x 8) 37.7 -> 38.9,
+  // 256 (8,192 x 896 x 2) 34.7 -> 37.3; and so do more segments per row (8,000 x 24 x
+  // 4, 31 -> 125 segments: 31.1 -> 31.8).  The statistics grow by less than 800 KB.
+  if (!f32 && 2 * H_RB * NS <= kCus)
+    for (int64_t units = 1; units < std::max<int64_t>(1, 256 / UK); ++units) {
+      const int64_t ns = ceil_div(U, units);
+      if (ns > kSegFew || H_RB * ns > kCus) continue;
+      NS = std::max(NS, ns);
+      break;
+    }
   // bytes == 0 marks an unsupported shape
   if (UK > INT32_MAX || U > INT32_MAX || H_RB * NS >= (int64_t(1) << 31)) return p;
   const size_t H = (size_t)d->n_kv_heads, m_pad = (size_t)(U * UK / c);

@@ -65,6 +65,25 @@ def test_many_segments(n, S, Hq, Hkv, d, c):
     check(n, S, Hq, Hkv, d, c, ckv.DTYPE_BF16, *inputs(n, S, Hq, Hkv, d, n), SCORE_RTOL_UNIT)
 
 
+@pytest.mark.parametrize("n,S,Hq,Hkv,d,c", [
+    (5, 1, 4, 1, 64, 4),          # one unit
+    (65, 3, 8, 2, 128, 8),        # two segments, the last of one key
+    (1000, 24, 14, 2, 64, 16),    # 16 segments of one stage, a short last chunk
+    (2048, 64, 28, 4, 128, 32),   # 32 segments, 256 workgroups: the most of each
+    (2049, 64, 28, 4, 128, 32),   # 33 units: segments of two stages, the last of one key
+    (4096, 128, 2, 1, 128, 64),   # 256 rows: no padding rows
+    (4101, 8, 14, 2, 64, 8),      # 65 units: segments of three stages
+    (1500, 2, 4, 2, 64, 128),     # units of two stages
+    (700, 9, 4, 2, 64, 96),       # units of three stages
+    (1024, 128, 40, 8, 128, 16),  # 96 workgroups of four stages become 192 of two
+    (1100, 200, 40, 8, 128, 16),  # 128 become 192 of three: two-stage ones exceed one per CU
+])
+def test_short_segments(n, S, Hq, Hkv, d, c):
+    """Launches with few workgroups, whose segments are one to three units."""
+    import paper_2601_13631_amd as ckv
+    check(n, S, Hq, Hkv, d, c, ckv.DTYPE_BF16, *inputs(n, S, Hq, Hkv, d, n), SCORE_RTOL_UNIT)
+
+
 @pytest.mark.parametrize("n,S", [(1024, 32), (5000, 20)])
 def test_fp32_segments(n, S):
     import paper_2601_13631_amd as ckv
@@ -72,6 +91,7 @@ def test_fp32_segments(n, S):
 
 
 @pytest.mark.parametrize("n,S,Hq,Hkv,d,c", [
+    (1000, 24, 14, 2, 64, 16),    # segments of one stage
     (9000, 60, 10, 2, 64, 16),    # 300 rows: blocks of four fold workgroups and of one
     (30011, 19, 7, 1, 128, 32),   # more segments than registers
 ])
