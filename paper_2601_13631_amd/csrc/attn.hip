@@ -882,7 +882,7 @@ AttnPlan make_attn_plan(const ckv_dims* d, int64_t k, bool with_suffix) {
   AttnPlan p{};
   const int G = d->n_q_heads / d->n_kv_heads;
   p.rows = G * d->n_suffix;
-  if (d->dtype == CKV_DTYPE_F32) {  // one wave per row, no splits
+  if (d->dtype == CKV_DTYPE_F32) {  // one workgroup per row, no splits
     p.n_splits = 1;
     return p;
   }
