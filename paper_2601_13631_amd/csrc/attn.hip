@@ -653,15 +653,24 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attn_kernel(AttnArgs a) {
       if (row_base + rr < a.R) *reinterpret_cast<uint4*>(obase + (int64_t)orow * D + seg * 8) = v;
     }
   }
-  // the reference the numerators were taken against (0 while no key was seen)
-  if (a.partial && row_ok && half == 0)
+  // The weight of a partial, exp2(ref) l, as (ref + e, l 2^-e) with l 2^-e in [1, 2)
+  // (0 where no key was seen): a reference far below the slice's maximum leaves a
+  // sum up to kGuard, by which the merge would multiply outputs as large as V.
+  if (a.partial && row_ok && half == 0) {
+    const uint32_t lb = __float_as_uint(l[0]);
+    if (l[0] > 0.f) {
+      ref += (float)((int)(lb >> 23) - 127);
+      l[0] = __uint_as_float((lb & 0x007fffffu) | 0x3f800000u);
+    }
     a.ml_part[((int64_t)split * a.Hkv + g) * a.R + row] = make_float2(ref, l[0]);
+  }
 }
 
 // Merges the splits of each row in split order: out = sum_s w_s Ohat_s with
-// w_s = e_s l_s / sum_s e_s l_s, e_s = exp2(m_s - max m), Ohat_s = O_s / l_s,
-// as a running merge over batches of kCombineBatch splits whose loads are in
-// flight together.  One thread per (row, 8 columns).
+// w_s = e_s l_s / sum_s e_s l_s, e_s = exp2(m_s - max m), Ohat_s = O_s / l_s and
+// (m_s, l_s) as stored (l_s in [1, 2): every e_s l_s is below 2), as a running
+// merge over batches of kCombineBatch splits whose loads are in flight together.
+// One thread per (row, 8 columns).
 constexpr int kCombineBatch = 8;
 
 template <int D>

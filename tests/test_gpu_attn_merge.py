@@ -1,0 +1,44 @@
+"""Attention slices whose reference is far below their maximum, against fp64.
+
+The numerators of a slice are taken against the largest logit of its first 32
+keys.  Here one later key in every 64 stands 10, 40 or 60 (log2 units) above
+those, inside the range that is not taken again, in one slice and in several that
+are merged; V of ordinary size and of 1.25 x 2^65, where at level 60 every slice's
+outputs stay inside fp32 and a merge by weights as large as the numerators would
+not.
+"""
+import math
+
+import pytest
+import torch
+
+from test_gpu_attn_stages import DEV, check, inputs
+
+pytestmark = pytest.mark.gpu
+
+
+def peaked(n, S, Hq, Hkv, d, level, v_scale):
+    """Small noise, and keys 40, 104, ... with logits of about `level` log2 units."""
+    q, k, v, ks, vs = inputs(S, Hq, Hkv, d, n, int(level) + n)
+    q, k, ks = 0.25 * q, 0.25 * k, 0.25 * ks
+    q[:, :, 0], k[:, :, 0], ks[:, :, 0] = 8, 0, 0
+    k[40::64, :, 0] = level * math.sqrt(d) / (8 * math.log2(math.e))
+    # a column's values have one sign, so nothing cancels in a merge; that a row's
+    # outputs have both keeps the sum over them, which guards a slice, small
+    sign = torch.where(torch.arange(d, device=DEV) // 8 % 2 == 0, 1, -1)
+    v, vs = (((1 + 0.1 * x.float().abs().clamp(max=1)) * sign * v_scale).to(x.dtype) for x in (v, vs))
+    return q, k, v, ks, vs
+
+
+@pytest.mark.parametrize("level", [10, 40, 60])
+@pytest.mark.parametrize("v_scale", [1.0, 1.25 * 2.0 ** 65])
+@pytest.mark.parametrize("n,d", [(256, 64), (256, 128), (1024, 64), (1024, 128)])
+def test_late_levels(n, d, v_scale, level):
+    import paper_2601_13631_amd as ckv
+    print(f"case n={n} d={d} V x {v_scale} level {level}", flush=True)
+    S, Hq, Hkv, c = 40, 4, 2, 32
+    k = n // c
+    merged = ckv.attn_workspace_bytes(ckv.make_dims(n, S, Hq, Hkv, d, c), k) > 0
+    assert merged == (n > 512)
+    sel = torch.arange(k, device=DEV, dtype=torch.int32)
+    check(n, S, Hq, Hkv, d, c, sel, *peaked(n, S, Hq, Hkv, d, level, v_scale))
