@@ -23,9 +23,9 @@
 // The K operand rows are loaded in a permuted order so that the registers a
 // lane holds after the first product are exactly the 8 consecutive keys the
 // second product needs from it -- no register shuffles between the two.
-// Splits write their normalised partial output O/l in bf16 (the output's own
-// type and range) plus (reference, l) in fp32; a combine kernel merges them in
-// split order (deterministic).
+// Splits write their partial output O in half precision with an exponent per row,
+// and (reference, l) in fp32; a combine kernel merges them in split order
+// (deterministic).
 //
 // What bounds it: the matrix cores (32 MFMAs of 32 cycles per wave and stage at
 // D = 128), the numerators' VALU work (112 instructions, the exponentials 8.6
@@ -118,7 +118,7 @@ struct AttnArgs {
   const uint16_t* ks;      // [S][Hkv][D]
   const uint16_t* vs;
   uint16_t* out;           // [S][Hq][D]
-  uint16_t* o_part;        // [splits][Hkv][R][D]: O / l, bf16
+  uint16_t* o_part;        // [splits][Hkv][R][D]: 2^-E O, fp16
   float2* ml_part;         // [splits][Hkv][R]: (reference, sum)
   int S, Hq, Hkv, G, R, n_splits, tiles_per_split, n_row_blocks;
   int partial;             // write split partials for a combine (else the output itself)
@@ -621,24 +621,55 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attn_kernel(AttnArgs a) {
   }
 
   // Output rows through LDS, so that every global store is a whole 16-byte
-  // piece of a row and 16 lanes cover a row: the wave's 32 rows (O/l in
-  // bf16) go to a stage buffer of its own, which every wave has finished
-  // reading (the barrier above).
+  // piece of a row and 16 lanes cover a row: the wave's 32 rows go to a stage
+  // buffer of its own, which every wave has finished reading (the barrier above).
+  float2 ml = make_float2(ref, 0.f);  // (reference 0 and no sum while no key was seen)
   {
     constexpr int kRow = D + 8;
     uint16_t* tile = wave == 0 ? k0 : wave == 1 ? k1 : wave == 2 ? v0 : v1;
-    const float inv = l[0] > 0.f ? 1.f / l[0] : 0.f;
+    // o[db][v] holds d = 32*db + 8*(v/4) + 4*half + v%4 of this lane's row
+    auto put_rows = [&](auto type, float scale) __attribute__((always_inline)) {
+      using T = decltype(type);
 #pragma unroll
-    for (int db = 0; db < D / 32; ++db)
+      for (int db = 0; db < D / 32; ++db)
 #pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4) {
-        __bf16 b[4];
+        for (int q4 = 0; q4 < 4; ++q4) {
+          T b[4];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) b[j] = (__bf16)(o[db][4 * q4 + j] * inv);
-        *reinterpret_cast<uint2*>(tile + (lane & 31) * kRow + 32 * db + 8 * q4 + 4 * half) =
-            *reinterpret_cast<uint2*>(b);
-      }
-    __builtin_amdgcn_wave_barrier();
+          for (int j = 0; j < 4; ++j) b[j] = (T)(o[db][4 * q4 + j] * scale);
+          *reinterpret_cast<uint2*>(tile + (lane & 31) * kRow + 32 * db + 8 * q4 + 4 * half) =
+              *reinterpret_cast<uint2*>(b);
+        }
+    };
+    if (a.partial) {
+      // A partial is stored as outputs 2^-E O in half precision, E the row's own (its
+      // largest output lies in [2^14, 2^15)), and as the pair of ref + e and of l 2^-e
+      // in [1, 2) with E - e for its exponent: against the reference ref + e the merge
+      // takes the sum from that mantissa and the outputs' power from that exponent.
+      // With e in the reference both are of V's size at most: a reference far below
+      // the slice's maximum leaves a sum up to kGuard, by which the merge would
+      // otherwise multiply outputs as large as V.  Halves in place of bf16 cost no
+      // bytes and 0.05 us, and take the partials' rounding, which was a third of the
+      // output's squared error, to a 64th (1,648 keys in 7 splits: 2.93e-3 -> 2.37e-3
+      // off fp64 in the 2-norm).
+      float om = 0.f;
+#pragma unroll
+      for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) om = fmaxf(om, fabsf(o[db][v]));
+      om = fmaxf(om, partner_f(om));
+      const uint32_t lb = __float_as_uint(l[0]);
+      const int e = (int)(lb >> 23) - 127;
+      // (E - e and E no lower than -110, so that both powers stay in fp32's range)
+      const int E = max((int)(__float_as_uint(om) >> 23) - 127 - 14, max(e, 0) - 110);
+      put_rows(_Float16{}, __uint_as_float((uint32_t)(127 - E) << 23));
+      if (l[0] > 0.f)
+        ml = make_float2(ref + (float)e,
+                         __uint_as_float((lb & 0x007fffffu) | (uint32_t)(E - e + 127) << 23));
+    } else {
+      put_rows(__bf16{}, l[0] > 0.f ? 1.f / l[0] : 0.f);
+    }
+    // 64 lanes = 64 / (D/8) rows x D/8 segments of 8
     constexpr int kSegs = D / 8, kRowsPerPass = 64 / kSegs;
     const int seg = lane % kSegs;
     const int row_base = rb * kBlockRows + wave * kWaveRows;
@@ -653,22 +684,11 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attn_kernel(AttnArgs a) {
       if (row_base + rr < a.R) *reinterpret_cast<uint4*>(obase + (int64_t)orow * D + seg * 8) = v;
     }
   }
-  // The weight of a partial, exp2(ref) l, as (ref + e, l 2^-e) with l 2^-e in [1, 2)
-  // (0 where no key was seen): a reference far below the slice's maximum leaves a
-  // sum up to kGuard, by which the merge would multiply outputs as large as V.
-  if (a.partial && row_ok && half == 0) {
-    const uint32_t lb = __float_as_uint(l[0]);
-    if (l[0] > 0.f) {
-      ref += (float)((int)(lb >> 23) - 127);
-      l[0] = __uint_as_float((lb & 0x007fffffu) | 0x3f800000u);
-    }
-    a.ml_part[((int64_t)split * a.Hkv + g) * a.R + row] = make_float2(ref, l[0]);
-  }
+  if (a.partial && row_ok && half == 0) a.ml_part[((int64_t)split * a.Hkv + g) * a.R + row] = ml;
 }
 
-// Merges the splits of each row in split order: out = sum_s w_s Ohat_s with
-// w_s = e_s l_s / sum_s e_s l_s, e_s = exp2(m_s - max m), Ohat_s = O_s / l_s and
-// (m_s, l_s) as stored (l_s in [1, 2): every e_s l_s is below 2), as a running
+// Merges the splits of each row in split order: out = sum_s w_s O_s / sum_s w_s l_s,
+// w_s = exp2(m_s - max m), from what a partial stores (see there), as a running
 // merge over batches of kCombineBatch splits whose loads are in flight together.
 // One thread per (row, 8 columns).
 constexpr int kCombineBatch = 8;
@@ -709,9 +729,10 @@ __global__ __launch_bounds__(256) void combine_kernel(const uint16_t* __restrict
         for (int j = 0; j < 8; ++j) acc[j] *= scale;
         M = ml[i].x;
       }
-      const float wgt = __builtin_amdgcn_exp2f(ml[i].x - M) * ml[i].y;
-      Lsum += wgt;
-      const __bf16* h = reinterpret_cast<const __bf16*>(&raw[i]);
+      const uint32_t y = __float_as_uint(ml[i].y);
+      const float w = __builtin_amdgcn_exp2f(ml[i].x - M), wgt = w * __uint_as_float(y & 0x7f800000u);
+      Lsum += w * __uint_as_float((y & 0x007fffffu) | 0x3f800000u);
+      const _Float16* h = reinterpret_cast<const _Float16*>(&raw[i]);
 #pragma unroll
       for (int j = 0; j < 8; ++j) acc[j] += wgt * (float)h[j];
     }
@@ -1015,7 +1036,7 @@ ckv_status launch_combine(const ckv_dims* d, const uint16_t* o_part, const float
 }
 
 // Split partials of a parted attention: splits [0, max_splits) of o_part
-// ([split][Hkv][R][D] bf16) then of ml_part ([split][Hkv][R] float2).
+// ([split][Hkv][R][D] fp16) then of ml_part ([split][Hkv][R] float2).
 size_t part_o_bytes(const ckv_dims* d, int64_t max_splits) {
   const int G = d->n_q_heads / d->n_kv_heads;
   return align_up((size_t)max_splits * d->n_kv_heads * G * d->n_suffix * d->head_dim *

@@ -1,0 +1,79 @@
+"""The bf16 attention is no further from fp64 than a plain evaluation with the
+roundings it must have.
+
+The plain evaluation takes `splits` equal slices of a row's keys: numerators
+against the maximum of a slice's first 64 keys, rounded to bf16 for the product
+with V, unrounded in the sum; the slices' outputs rounded to bf16 when there are
+several; the merged output rounded to bf16.  Everything else in fp64, here on the
+GPU.  Both errors are 2-norms over all outputs (100,000 or more), which differ by
+under 0.1% where the roundings are the same; 0.2% is allowed.
+"""
+import math
+
+import pytest
+import torch
+
+from gpu_common import DEV, workspace
+from test_gpu_attn_stages import attention_f64, inputs
+
+pytestmark = pytest.mark.gpu
+
+
+def bf16(x):
+    return x.to(torch.bfloat16).double()
+
+
+def plain(q, k, v, ks, vs, splits):
+    S, Hq, d = q.shape
+    n, Hkv = k.shape[:2]
+    G = Hq // Hkv
+    tiles = -(-(n + S) // 64)
+    per = 64 * -(-tiles // splits)
+    hidden = (torch.arange(n + S, device=DEV)[None, :] - n) > torch.arange(S, device=DEV)[:, None]
+    out = torch.empty((S, Hq, d), dtype=torch.float64, device=DEV)
+    for h in range(Hq):
+        kk = torch.cat((k[:, h // G], ks[:, h // G])).double().t().contiguous()
+        vv = torch.cat((v[:, h // G], vs[:, h // G])).double()
+        x = (q[:, h].double() @ kk) * (math.log2(math.e) / math.sqrt(d))
+        x = x.masked_fill(hidden, -math.inf)
+        parts = []
+        for at in range(0, n + S, per):
+            y = x[:, at:at + per]
+            m = y[:, :64].amax(1, keepdim=True)
+            m = torch.where(m > -math.inf, m, y.amax(1, keepdim=True)).clamp(min=-1e30)
+            p = torch.exp2(y - m)
+            l = p.sum(1, keepdim=True)
+            o = bf16(p.float()) @ vv[at:at + per] / l.clamp(min=1e-300)
+            parts.append((m, l, bf16(o) if per < n + S else o))
+        top = torch.stack([m for m, _, _ in parts]).amax(0)
+        w = [torch.exp2(m - top) * l for m, l, _ in parts]
+        out[:, h] = bf16(sum(wi * o for wi, (_, _, o) in zip(w, parts)) / sum(w))
+    return out
+
+
+@pytest.mark.parametrize("n,S,Hq,Hkv,d,c,splits", [
+    (1648, 128, 14, 2, 64, 16, 7),
+    (3008, 19, 28, 4, 128, 32, 12),
+    (8000, 64, 16, 4, 128, 64, 9),
+])
+def test_rounding(n, S, Hq, Hkv, d, c, splits):
+    import paper_2601_13631_amd as ckv
+    print(f"case n={n} S={S} heads={Hq}:{Hkv} d={d} c={c}", flush=True)
+    q, k, v, ks, vs = inputs(S, Hq, Hkv, d, n, n)
+    gen = torch.Generator(DEV).manual_seed(n)
+    u = torch.nn.functional.normalize(torch.randn(d, generator=gen, device=DEV), dim=0)
+    q = (q.float() + u).to(q.dtype)
+    k = k.float()
+    k[torch.rand(n // c, generator=gen, device=DEV).lt(0.25).repeat_interleave(c)] += 1.5 * u  # heavy chunks
+    k = k.to(q.dtype)
+    dims = ckv.make_dims(n, S, Hq, Hkv, d, c)
+    sel = torch.arange(n // c, device=DEV, dtype=torch.int32)
+    ws = workspace(ckv.attn_workspace_bytes(dims, n // c))
+    assert (ckv.attn_workspace_bytes(dims, n // c) > 0) == (splits > 1)
+    out = torch.empty_like(q)
+    ckv.sparse_prefill_attn(dims, q, k, v, sel, n // c, ks, vs, out, ws)
+    torch.cuda.synchronize()
+    ref = attention_f64(q, k, v, ks, vs, torch.ones(n, dtype=torch.bool, device=DEV))
+    got, want = (float((x.double() - ref).norm() / ref.norm()) for x in (out, plain(q, k, v, ks, vs, splits)))
+    print(f"  relative error {got:.4e}, the plain evaluation's {want:.4e}", flush=True)
+    assert got <= 1.002 * want
