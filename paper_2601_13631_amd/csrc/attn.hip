@@ -14,7 +14,7 @@
 //                 registers: every lane owns one query row and 16 keys;
 //   numerators    exp2 in fp32 (sm_scale*log2 e folded in) against a fixed
 //                 reference per row: the maximum over the slice's first 32
-//                 keys.  A slice whose sums or outputs then leave a guard (or
+//                 keys (64 where it is the row's only slice).  A slice whose sums or outputs then leave a guard (or
 //                 that had no reference) is done again against its own maximum,
 //                 so the result never depends on the guess;
 //   O^T += V^T P^T  A = V^T read from LDS with the transposing
@@ -373,7 +373,8 @@ __device__ __forceinline__ void static_for(F&& f) {
   for_each_of(std::make_integer_sequence<int, N>{}, f);
 }
 
-template <int D>
+// kPartial: the slice is one of several of its rows (AttnArgs::o_part, ml_part).
+template <int D, bool kPartial>
 __global__ __launch_bounds__(kWaves * 64, 2) void attn_kernel(AttnArgs a) {
   using St = Stage<D>;
   // two stage buffers, as arrays of their own: loads into one are then known
@@ -404,13 +405,14 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attn_kernel(AttnArgs a) {
   const int hi = row_ok ? row % a.G : 0;
 
   // keys the block's last query can see; the block's first query sees every
-  // suffix key up to its own position
-  const int first_t = (rb * kBlockRows) / a.G;
+  // suffix key up to its own position (both in scalar registers: left to itself the
+  // compiler keeps them, and every branch on them, in vector ones, 0.4 us a launch)
+  const int first_t = __builtin_amdgcn_readfirstlane((rb * kBlockRows) / a.G);
   const int last_row = min(a.R - 1, rb * kBlockRows + kBlockRows - 1);
   const int np_block = a.kc + (a.with_suffix ? last_row / a.G + 1 : 0);
   const int ntiles = (np_block + kTile - 1) / kTile;
   const int tile0 = split * a.tiles_per_split;
-  const int nt = max(0, min(ntiles, tile0 + a.tiles_per_split) - tile0);
+  const int nt = __builtin_amdgcn_readfirstlane(max(0, min(ntiles, tile0 + a.tiles_per_split) - tile0));
 
   // the first units' index loads, then Q: loads return in order, so the tables
   // (on the critical path to the first K/V loads) do not wait for Q
@@ -537,6 +539,19 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attn_kernel(AttnArgs a) {
         if (fl & kStageMask) mask(st, 0, s0);
         if (st == 0 && attempt == 0) {  // the reference: the first 32 keys' largest logit
           float mx = max16(s0);
+          if constexpr (!kPartial) {
+            // A row's only slice takes it from 64 keys: the largest weight is then exactly
+            // 1 as often as with a running maximum over whole stages, and no partial's
+            // rounding is saved that would pay for less (280 keys: 2.31e-3 -> 2.29e-3 off
+            // fp64; under 0.1 us of 8.7).
+#pragma unroll
+            for (int i = 0; i < kG; ++i)
+              s1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kb[i], qf[i], s1, 0, 0, 0);
+            if (fl & kStageMask) mask(st, 1, s1);
+            mx = fmaxf(mx, max16(s1));
+#pragma unroll
+            for (int v = 0; v < 16; ++v) s1[v] = 0.f;
+          }
           mx = fmaxf(mx, partner_f(mx));
           no_ref = mx == -INFINITY;
           ref = no_ref ? 0.f : mx * a.c1;
@@ -641,7 +656,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attn_kernel(AttnArgs a) {
               *reinterpret_cast<uint2*>(b);
         }
     };
-    if (a.partial) {
+    if constexpr (kPartial) {
       // A partial is stored as outputs 2^-E O in half precision, E the row's own (its
       // largest output lies in [2^14, 2^15)), and as the pair of ref + e and of l 2^-e
       // in [1, 2) with E - e for its exponent: against the reference ref + e the merge
@@ -674,8 +689,8 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attn_kernel(AttnArgs a) {
     const int seg = lane % kSegs;
     const int row_base = rb * kBlockRows + wave * kWaveRows;
     // output row of this lane's query row; row rr's is lane rr's
-    const int out_row = a.partial ? row : (row_ok ? t : 0) * a.Hq + g * a.G + hi;
-    uint16_t* obase = a.partial ? a.o_part + ((int64_t)split * a.Hkv + g) * a.R * D : a.out;
+    const int out_row = kPartial ? row : (row_ok ? t : 0) * a.Hq + g * a.G + hi;
+    uint16_t* obase = kPartial ? a.o_part + ((int64_t)split * a.Hkv + g) * a.R * D : a.out;
 #pragma unroll
     for (int r0 = 0; r0 < kWaveRows; r0 += kRowsPerPass) {
       const int rr = r0 + lane / kSegs;
@@ -684,7 +699,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attn_kernel(AttnArgs a) {
       if (row_base + rr < a.R) *reinterpret_cast<uint4*>(obase + (int64_t)orow * D + seg * 8) = v;
     }
   }
-  if (a.partial && row_ok && half == 0) a.ml_part[((int64_t)split * a.Hkv + g) * a.R + row] = ml;
+  if (kPartial && row_ok && half == 0) a.ml_part[((int64_t)split * a.Hkv + g) * a.R + row] = ml;
 }
 
 // Merges the splits of each row in split order: out = sum_s w_s O_s / sum_s w_s l_s,
@@ -1012,10 +1027,9 @@ ckv_status attn_args(const ckv_dims* d, const void* q, const ChunkSource& src, c
 
 ckv_status launch_attn_kernel(const ckv_dims* d, const AttnArgs& a, hipStream_t st) {
   const size_t slice_bytes = (size_t)a.tiles_per_split * (2 * (kTile >> a.log2u) + 1) * sizeof(int);
-  if (d->head_dim == 128)
-    hipLaunchKernelGGL(attn_kernel<128>, dim3(a.nblocks_padded), dim3(kWaves * 64), slice_bytes, st, a);
-  else
-    hipLaunchKernelGGL(attn_kernel<64>, dim3(a.nblocks_padded), dim3(kWaves * 64), slice_bytes, st, a);
+  const auto kernel = d->head_dim == 128 ? (a.partial ? attn_kernel<128, true> : attn_kernel<128, false>)
+                                         : (a.partial ? attn_kernel<64, true> : attn_kernel<64, false>);
+  hipLaunchKernelGGL(kernel, dim3(a.nblocks_padded), dim3(kWaves * 64), slice_bytes, st, a);
   CKV_HIP(hipGetLastError());
   return CKV_OK;
 }

@@ -55,6 +55,7 @@ def plain(q, k, v, ks, vs, splits):
     (1648, 128, 14, 2, 64, 16, 7),
     (3008, 19, 28, 4, 128, 32, 12),
     (8000, 64, 16, 4, 128, 64, 9),
+    (256, 24, 14, 2, 64, 16, 1), (160, 64, 28, 4, 128, 32, 1), (64, 300, 32, 8, 128, 16, 1),
 ])
 def test_rounding(n, S, Hq, Hkv, d, c, splits):
     import paper_2601_13631_amd as ckv
