@@ -42,3 +42,15 @@ def test_late_levels(n, d, v_scale, level):
     assert merged == (n > 512)
     sel = torch.arange(k, device=DEV, dtype=torch.int32)
     check(n, S, Hq, Hkv, d, c, sel, *peaked(n, S, Hq, Hkv, d, level, v_scale))
+
+
+@pytest.mark.parametrize("n,d", [(256, 64), (256, 128), (1024, 64), (1024, 128)])
+def test_outputs_overflow(n, d):
+    """Numerators of 2^60 times finite V of 2^70, positive and negative from peak to
+    peak: a slice's sum stays inside its range while its outputs become infinite and,
+    where both signs meet, NaN."""
+    print(f"case n={n} d={d}", flush=True)
+    S, Hq, Hkv, c = 40, 4, 2, 32
+    q, k, v, ks, vs = peaked(n, S, Hq, Hkv, d, 60, 2.0 ** 70)
+    v[104::128] *= -1
+    check(n, S, Hq, Hkv, d, c, torch.arange(n // c, device=DEV, dtype=torch.int32), q, k, v, ks, vs)
