@@ -489,6 +489,15 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attn_kernel(AttnArgs a) {
     mask_logits(a, valids + st * upst, pos00 + st * kTile, sub, t, s);
   };
 
+  // whether this lane's query sees a key of the slice
+  auto sees_key = [&]() {
+    for (int i = 0; i < n_units; ++i) {
+      const int pos = pos00 + (i << a.log2u);
+      if (valids[i] > 0) return pos < a.kc || t >= pos - a.kc;  // later units: later positions
+    }
+    return false;
+  };
+
   bool no_ref = false;  // the reference had to be taken from no key at all
   for (int attempt = 0;; ++attempt) {
 #pragma unroll
@@ -598,7 +607,8 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attn_kernel(AttnArgs a) {
     // The reference is the first keys' maximum: a later logit far above it can
     // push the sum past the guard or an output past fp32, and a row whose first
     // keys are all hidden has none.  Then once more, against the slice's own
-    // maximum.
+    // maximum.  (A row that sees no key of the slice, as those before a slice that
+    // begins inside their block's part of the suffix, has nothing to do again.)
     if (attempt) break;
     // (a sum over the outputs is inf or NaN if one of them is)
     float any[4] = {0.f, 0.f, 0.f, 0.f};
@@ -609,7 +619,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attn_kernel(AttnArgs a) {
     const uint32_t total = __float_as_uint((any[0] + any[1]) + (any[2] + any[3]));
     const bool bad = (total & 0x7f800000u) == 0x7f800000u ||
                      (__float_as_uint(l[0]) & 0x7fffffffu) > __float_as_uint(kGuard) ||
-                     (no_ref && l[0] < 1.f / kGuard);
+                     (no_ref && l[0] < 1.f / kGuard && sees_key());
     if (!__syncthreads_or(bad)) break;
     float mx = -INFINITY;
     for (int st = 0; st < nt; ++st) {

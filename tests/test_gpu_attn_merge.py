@@ -54,3 +54,32 @@ def test_outputs_overflow(n, d):
     q, k, v, ks, vs = peaked(n, S, Hq, Hkv, d, 60, 2.0 ** 70)
     v[104::128] *= -1
     check(n, S, Hq, Hkv, d, c, torch.arange(n // c, device=DEV, dtype=torch.int32), q, k, v, ks, vs)
+
+
+def test_rows_without_keys_are_not_redone():
+    """A slice that begins inside a block's part of the suffix: the block's first rows
+    see none of it, which is no reason to do it again.  That a slice was done again
+    shows in its other rows' rounding (another reference), here by a row that makes
+    it so."""
+    import paper_2601_13631_amd as ckv
+    n, S, d, c = 128, 512, 64, 32
+    dims = ckv.make_dims(n, S, 1, 1, d, c)
+    ws_bytes = ckv.attn_workspace_bytes(dims, n // c)
+    # two slices of 5 stages: the second begins at suffix token 192, rows 128..255 are a block
+    assert ws_bytes == 2 * S * (d * 2 + 8)
+    sel = torch.arange(n // c, device=DEV, dtype=torch.int32)
+    q, k, v, ks, vs = inputs(S, 1, 1, d, n, 5)
+    q[:, :, 0], k[:, :, 0], ks[:, :, 0] = 0, 0, 0
+    ks[250, :, 0] = 8
+    redo = q.clone()
+    redo[255, :, 0] = 127
+    outs = []
+    for x in (q, redo):
+        check(n, S, 1, 1, d, c, sel, x, k, v, ks, vs)
+        outs.append(torch.empty_like(x))
+        ckv.sparse_prefill_attn(dims, x, k, v, sel, n // c, ks, vs, outs[-1],
+                                torch.empty(ws_bytes, dtype=torch.uint8, device=DEV))
+    torch.cuda.synchronize()
+    same = (outs[0] == outs[1]).all(dim=-1).flatten()
+    assert same[:192].all() and same[256:].all()
+    assert not same[192:255].all()
