@@ -14,9 +14,10 @@
 //                 registers: every lane owns one query row and 16 keys;
 //   numerators    exp2 in fp32 (sm_scale*log2 e folded in) against a fixed
 //                 reference per row: the maximum over the slice's first 32
-//                 keys (64 where it is the row's only slice).  A slice whose sums or outputs then leave a guard (or
-//                 that had no reference) is done again against its own maximum,
-//                 so the result never depends on the guess;
+//                 keys (64 where it is the row's only slice).  A slice whose
+//                 sums or outputs then leave a guard (or that had no
+//                 reference) is done again against its own maximum, so that
+//                 the guess decides no more than roundings;
 //   O^T += V^T P^T  A = V^T read from LDS with the transposing
 //                 ds_read_b64_tr_b16, B = P^T straight from the softmax
 //                 registers.
@@ -42,6 +43,13 @@
 // two waves of 32 rows 3,440), and a loop that spreads the numerators over all
 // 32 MFMAs by running a product of the next stage early (128K 295 against 302 us
 // of the loop below, small grids 10% slower for its longer prologue).
+//
+// A slice that is done again costs its workgroup a pass over its K rows and a second
+// pass of everything.  With every slice done again (in each 64 keys one 90 log2
+// units above the others): 32K layer 31 -> 49 us, 64K 111 -> 267, 8K 11.5 -> 19.4,
+// 8,000 tokens x 32 heads 77 -> 176; a running maximum took 32, 143, 12.1 and 103 us
+// on these inputs.  It takes a logit 64 log2 units (44 nats) above all of the slice's
+// first keys.
 
 #include <atomic>
 #include <type_traits>
@@ -208,14 +216,15 @@ struct LoadLane {
   int key0, kcol, vcol;
 };
 
-// Loads the K and V rows of the stage at position pos0 into dk and dv.  base: the
-// unit table entries of this lane's keys; bases/valids: the stage's unit tables.
+// Loads the K rows of the stage at position pos0 into dk and (kV) its V rows into
+// dv.  base: the unit table entries of this lane's keys; bases/valids: the stage's
+// unit tables.
 // A stage of 64 rows of one source (the common case) goes through one buffer
 // resource per tensor with 32-bit byte offsets.  Any other takes the lanes of
 // the two sources in turn (a key without a row reads its unit's last, or suffix
 // row 0; its weight is forced to 0), and with a source past 4 GiB a resource per
 // group of 4 keys, which share a unit.
-template <int D>
+template <int D, bool kV = true>
 __device__ __forceinline__ void stage_load(const AttnArgs& a, int flags, const int* base,
                                            const int* bases, const int* valids, int pos0, int wave,
                                            const LoadLane& ll, uint16_t* dk, uint16_t* dv) {
@@ -232,7 +241,8 @@ __device__ __forceinline__ void stage_load(const AttnArgs& a, int flags, const i
     for (int p = 0; p < St::kPer; ++p) {
       const uint32_t soff = (p * St::kKeyStep & umask) * a.row_bytes;
       buffer_to_lds(kr, (uint32_t)base[p] + (uint32_t)ll.kcol, soff, dk + p * St::kKeyStep * D);
-      buffer_to_lds(vr, (uint32_t)base[p] + (uint32_t)ll.vcol, soff, dv + p * St::kKeyStep * D);
+      if constexpr (kV)
+        buffer_to_lds(vr, (uint32_t)base[p] + (uint32_t)ll.vcol, soff, dv + p * St::kKeyStep * D);
     }
     return;
   }
@@ -255,10 +265,12 @@ __device__ __forceinline__ void stage_load(const AttnArgs& a, int flags, const i
                                         : 0u;
       if (valid[p] > 0 && pos0 + key < a.kc) {
         buffer_to_lds(kp, off + (uint32_t)kcol, 0, dk + p * St::kKeyStep * D);
-        buffer_to_lds(vp, off + (uint32_t)vcol, 0, dv + p * St::kKeyStep * D);
+        if constexpr (kV)
+          buffer_to_lds(vp, off + (uint32_t)vcol, 0, dv + p * St::kKeyStep * D);
       } else {
         buffer_to_lds(ks, off + (uint32_t)kcol, 0, dk + p * St::kKeyStep * D);
-        buffer_to_lds(vs, off + (uint32_t)vcol, 0, dv + p * St::kKeyStep * D);
+        if constexpr (kV)
+          buffer_to_lds(vs, off + (uint32_t)vcol, 0, dv + p * St::kKeyStep * D);
       }
     }
     return;
@@ -278,7 +290,8 @@ __device__ __forceinline__ void stage_load(const AttnArgs& a, int flags, const i
     // (the offsets stay inside one unit: no bound is needed beyond it)
     if (kGroups == 1 || (int)((threadIdx.x & 63) / (64 / kGroups)) == q) {
       buffer_to_lds(raw_rsrc(kp, 0xffffffffu), (uint32_t)kcol + in_unit, 0, dk + p * St::kKeyStep * D);
-      buffer_to_lds(raw_rsrc(vp, 0xffffffffu), (uint32_t)vcol + in_unit, 0, dv + p * St::kKeyStep * D);
+      if constexpr (kV)
+        buffer_to_lds(raw_rsrc(vp, 0xffffffffu), (uint32_t)vcol + in_unit, 0, dv + p * St::kKeyStep * D);
     }
   }
 }
@@ -626,7 +639,8 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attn_kernel(AttnArgs a) {
       int r[St::kPer];
       read_bases(st, r);
       const int f = flags_of(st);
-      load_stage(st, f, r, k0, v0);
+      stage_load<D, false>(a, f, r, bases + st * upst, valids + st * upst, pos00 + st * kTile, wave, ll,
+                           k0, v0);
       stage_barrier();
 #pragma unroll
       for (int sub = 0; sub < 2; ++sub) {
