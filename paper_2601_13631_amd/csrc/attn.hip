@@ -956,7 +956,11 @@ int64_t attn_blocks(const ckv_dims* d) {
 }
 
 // The most splits that make_attn_plan may take: those that give 512 workgroups of 4
-// stages or more, or that hold a slice to 16 stages.
+// stages or more, or that hold a slice to 16 stages.  They bound the partials'
+// workspace.  The smallest launches would gain from shorter slices (15 stages of 2
+// workgroups: 8.3 us in 8 splits, 10.5 in the 3 taken; 20 of 16: 13.6 in 7, 14.9 in
+// 5), others not (48 of 8, which the model below expects to gain 14% from 24 splits:
+// 14.7 us, 14.5 in the 12 taken).
 int64_t attn_most_splits(const ckv_dims* d, int64_t ntiles) {
   return std::max(std::max<int64_t>(1, std::min(512 / attn_blocks(d), ntiles / 4)), ceil_div(ntiles, 16));
 }
@@ -976,9 +980,10 @@ AttnPlan make_attn_plan(const ckv_dims* d, int64_t k, bool with_suffix) {
   // 512 workgroups run at once, two per CU, each for its stages (two of them
   // take 3,440 cycles per stage, one alone on its CU 2,100) and a fixed part
   // (tables, first loads, output); and every split's partials are merged (14
-  // splits of 40,960 rows took 25 us, 3 of them 8).  At most the splits that
-  // give 512 workgroups of 4 stages or more, or that hold a slice to 16 stages:
-  // more never won, and the partials' workspace stays within that of those.
+  // splits of 40,960 rows took 25 us, 3 of them 8).  The constants are of head_dim
+  // 128; at 64, where a stage has half the MFMAs and three workgroups fit a CU, five
+  // of six plans were within 8% of the best of nine split counts (the sixth is the
+  // launch of 2 workgroups above).
   constexpr double kFixed = 15000, kStage = 3440, kFixedAlone = 12500, kStageAlone = 2100;
   constexpr double kCombine = 5500, kMergeBytes = 5000;
   const double merge = (double)d->n_kv_heads * p.rows * d->head_dim * 2 / kMergeBytes;
