@@ -28,6 +28,10 @@ STAGES = ("score", "finalize", "select", "move", "attn")
 
 if not os.path.exists(LIB_PATH):
     raise ImportError(f"libckv.so not built at {LIB_PATH}; run `python paper_2601_13631_amd/build.py`")
+# torch first: libckv.so then binds to the HIP runtime that torch has loaded.  The
+# other way round the process holds two, and what one allocates the other faults on.
+import torch  # noqa: E402,F401
+
 _lib = ctypes.CDLL(LIB_PATH)
 
 
