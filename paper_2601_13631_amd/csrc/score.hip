@@ -672,7 +672,10 @@ __device__ __forceinline__ Segment segment_of(const ScoreWork& wk, int64_t n, in
 // by exact powers of two).  Against 256 rows per workgroup with every
 // segment in one thread: 5.3 -> 4.0 us at 32 segments of 896 rows x 2 heads, 5.7 ->
 // 4.8 at 6 of 2,560 x 8, and 11.6 us for 58 segments of 133 rows x 4 became 7.2 for
-// 117; three segments of 5,120 rows x 8 take 5.6 instead of 4.9.
+// 117.  Up to three segments leave waves without one while all pay for the merge:
+// there each wave folds 64 rows of its own (three of 5,120 rows x 8: 5.4 us merged,
+// 4.8; two of 7,500 x 8: 5.9, 4.9; one of 15,000 x 8: 9.1, 5.0; at four, 3,250 x 8, the
+// merge takes 4.8 and own rows 4.7).
 
 // exp2(mc - M) for whole-number references mc <= M: an exact power of two
 // (zero once it is below the smallest subnormal).
@@ -693,12 +696,12 @@ struct FoldRegs {
   double zz[B];
 };
 
-template <int B>
+template <int B, int STRIDE = kWaves>
 __device__ __forceinline__ void fold_load(const float* mc, const double* z, const ScoreWork& wk,
                                           int64_t base, int s0, FoldRegs<B>& r) {
 #pragma unroll
   for (int i = 0; i < B; ++i) {
-    const int s = s0 + i * kWaves;
+    const int s = s0 + i * STRIDE;
     const bool ok = s < wk.NS;  // uniform
     r.v[i] = ok ? mc[base + (int64_t)s * wk.ldp] : -INFINITY;
     r.zz[i] = ok ? z[base + (int64_t)s * wk.ldp] : 0.0;
@@ -730,12 +733,12 @@ __device__ __forceinline__ void fold_sum(const FoldRegs<B>& r, float& Mw, double
   for (int i = 0; i < B; ++i) Zw += seg_factor(r.v[i], Mw) * r.zz[i];
 }
 
-template <int B>
+template <int B, int STRIDE = kWaves>
 __device__ __forceinline__ void fold_store(double* z, const ScoreWork& wk, int64_t base, int s0,
                                            const FoldRegs<B>& r, float M, double inv) {
 #pragma unroll
   for (int i = 0; i < B; ++i) {
-    const int s = s0 + i * kWaves;
+    const int s = s0 + i * STRIDE;
     if (s < wk.NS) z[base + (int64_t)s * wk.ldp] = seg_factor(r.v[i], M) * inv;
   }
 }
@@ -776,6 +779,7 @@ __device__ __forceinline__ void fold_rows_batched(const float* mc, double* z, co
   }
 }
 
+constexpr int kFoldOwn = 3;    // up to this many segments a wave folds 64 rows of its own
 constexpr int kFoldFew = 8;    // segments per wave in registers, few segments
 constexpr int kFoldMany = 16;  // and per batch, many segments
 
@@ -828,20 +832,26 @@ __global__ __launch_bounds__(kWaves * 64, 2) void score_bf16_kernel(ScoreArgs a)
 // own maximum, two passes) any of their segments whose chunk sums left the guard
 // in the main pass -- almost never -- then folds the segments.  In a redo all
 // four waves stage the keys and compute the same 64 rows (and store the same values).
-template <int D, int MODE>
+// OWN (up to kFoldOwn segments): one workgroup per row block, each wave folding 64
+// rows of its own, so that no wave is without a segment and nothing is merged; a wave
+// past the last rows takes part in a redo with those before it.
+template <int D, int MODE, bool OWN>
 __global__ __launch_bounds__(kWaves * 64, 2) void score_fold_kernel(ScoreArgs a) {
   __shared__ __attribute__((aligned(16))) uint16_t lds[2 * kStage * SubtileLds<D>::kRow];
-  __shared__ FoldLds sh;
-  const int groups = a.w.ldp / kWaveRows;  // per KV head
-  const int g = blockIdx.x / groups, my_row0 = (blockIdx.x % groups) * kWaveRows;
-  const int rbh = g * a.w.RB + my_row0 / kBlockRows;
   const int wave = threadIdx.x >> 6;
+  const int groups = OWN ? a.w.RB : a.w.ldp / kWaveRows;  // per KV head
+  const int g = blockIdx.x / groups;
+  const int row0 = (blockIdx.x % groups) * (OWN ? kBlockRows : kWaveRows) + (OWN ? wave * kWaveRows : 0);
+  const int my_row0 = min(row0, a.w.ldp - kWaveRows);
+  const int rbh = g * a.w.RB + my_row0 / kBlockRows;
   const int64_t base = (int64_t)g * a.w.NS * a.w.ldp + my_row0 + (threadIdx.x & 63);
   // all flags of the block, and (speculatively) the rows' statistics, in one
   // round trip; nothing flagged is the common case
-  const bool few = a.w.NS <= kFoldFew * kWaves;
-  FoldRegs<kFoldFew> r;
-  if (few) fold_load<kFoldFew>(a.mc, a.z, a.w, base, wave, r);
+  constexpr int kB = OWN ? kFoldOwn : kFoldFew, kStride = OWN ? 1 : kWaves;
+  const int s0 = OWN ? 0 : wave;
+  const bool few = a.w.NS <= kB * kStride;
+  FoldRegs<kB> r;
+  if (few) fold_load<kB, kStride>(a.mc, a.z, a.w, base, s0, r);
   int any = 0;
   for (int s = threadIdx.x; s < a.w.NS; s += blockDim.x) any |= a.flags[rbh * a.w.NS + s];
   const bool redo = __syncthreads_or(any);
@@ -857,13 +867,20 @@ __global__ __launch_bounds__(kWaves * 64, 2) void score_fold_kernel(ScoreArgs a)
       store_stats(a, g, s, my_row0, st);
       __syncthreads();
     }
+    if (few) fold_load<kB, kStride>(a.mc, a.z, a.w, base, s0, r);  // the rows as redone
   }
-  if (!few) {
-    fold_rows_batched<kFoldMany>(a.mc, a.z, a.w, base, sh);
-    return;
+  if constexpr (OWN) {
+    float M;
+    double Z;
+    fold_sum<kB>(r, M, Z);
+    if (row0 < a.w.ldp) fold_store<kB, 1>(a.z, a.w, base, 0, r, M, 1.0 / Z);
+  } else {
+    __shared__ FoldLds sh;
+    if (few)
+      fold_rows<kB>(a.z, a.w, base, sh, r);
+    else
+      fold_rows_batched<kFoldMany>(a.mc, a.z, a.w, base, sh);
   }
-  if (redo) fold_load<kFoldFew>(a.mc, a.z, a.w, base, wave, r);  // the rows as redone
-  fold_rows<kFoldFew>(a.z, a.w, base, sh, r);
 }
 
 // fp32 path: the main kernel already redid overflowing segments; fold only.
@@ -1320,12 +1337,16 @@ ckv_status launch_score(const ckv_dims* d, const void* q, const void* k, double*
     a.nwg_padded = (uint32_t)align_up(nwg, 8);
     a.tstamp = main_span;
     dim3 grid(a.nwg_padded), block(kWaves * 64);
-    const dim3 fold_grid((unsigned)(d->n_kv_heads * (p.w.ldp / kWaveRows)));
+    const bool own = p.w.NS <= kFoldOwn;
+    const dim3 fold_grid((unsigned)(d->n_kv_heads * (own ? p.w.RB : p.w.ldp / kWaveRows)));
 #define CKV_SCORE_LAUNCH(DD, MM)                                                           \
   do {                                                                                     \
     hipLaunchKernelGGL((score_bf16_kernel<DD, MM>), grid, block, 0, st, a);                \
     if (main_stop) CKV_HIP(hipEventRecord(main_stop, st));                                \
-    hipLaunchKernelGGL((score_fold_kernel<DD, MM>), fold_grid, block, 0, st, a);           \
+    if (own)                                                                               \
+      hipLaunchKernelGGL((score_fold_kernel<DD, MM, true>), fold_grid, block, 0, st, a);   \
+    else                                                                                   \
+      hipLaunchKernelGGL((score_fold_kernel<DD, MM, false>), fold_grid, block, 0, st, a);  \
   } while (0)
     if (d->head_dim == 128) {
       switch (mode) {
