@@ -11,9 +11,10 @@
 // VALU instructions a key) and meets at two barriers.  16,384 scores: 75 us with
 // 256 threads and the keys in LDS, whose per-bin atomics nearly all collide (a
 // layer's scores share their high bits), 26 us with 16 keys per thread in
-// registers; 32,768: 192 -> 39 us; 100,000, where 1,024 threads re-read instead of
-// 256: 749 -> 238 us.  (The same rounds on 32-bit windows of the keys, with the 64-bit ones behind for
-// what they leave open, took 28 us, and 6.5 against 6.1 us at 1,024 scores.)
+// registers; 32,768: 192 -> 33 us; 100,000, where 1,024 threads re-read instead of
+// 256: 749 -> 238 us.  (The same rounds on 32-bit windows of the keys, with the
+// 64-bit ones behind for what they leave open, took 28 us, and 6.5 against 6.1 us
+// at 1,024 scores.)
 
 #include "select_regs.h"
 

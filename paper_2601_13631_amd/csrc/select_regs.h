@@ -73,21 +73,19 @@ __device__ __forceinline__ uint32_t pair_sum32(uint32_t x) {
   return r[0] + r[1];
 }
 
-// The wave's count of keys per digit value 0..15 (digit 16: not a candidate),
-// for E keys per lane: each lane counts its digits in 4-bit fields of one 64-bit
-// word per kGroup keys, the fields are spread to bytes (and added up over the
-// groups), and summed over each row of 16 lanes by DPP, in bytes while 16 * E <=
-// 255, else widened to 16-bit fields first, then over the four rows by the
-// permlane swaps.  Lane 15 returns digit pair (2i, 2i + 1) in cnt[i] (low, high
-// half).
-template <int E>
-__device__ __forceinline__ void wave_digit_counts(const int (&cd)[E], uint32_t (&cnt)[8]) {
-  constexpr int kGroup = E <= 15 ? E : 8;
-  static_assert(E % kGroup == 0 && E <= 128, "4-bit per-lane fields, byte sums");
-  // byte j of by[q]: digit 8 * (q / 2) + 2 * j + (q % 2)
-  uint32_t by[4] = {0u, 0u, 0u, 0u};
+// A wave's count of keys per digit value 0..15 (digit 16: not a candidate): each lane
+// counts its digits in 4-bit fields of one 64-bit word per kGroup keys, the fields are
+// spread to bytes and added up over the groups (add_digits; byte j of by[q]: digit
+// 8 * (q / 2) + 2 * j + (q % 2)), and summed (wave_digit_counts, E keys per lane) over
+// each row of 16 lanes by DPP, in bytes while 16 * E <= 255, else widened to 16-bit
+// fields first, then over the four rows by the permlane swaps.  Lane 15 returns
+// digit pair (2i, 2i + 1) in cnt[i] (low, high half).
+template <int N>
+__device__ __forceinline__ void add_digits(const int (&cd)[N], uint32_t (&by)[4]) {
+  constexpr int kGroup = N <= 15 ? N : 8;
+  static_assert(N % kGroup == 0, "4-bit per-lane fields");
 #pragma unroll
-  for (int e0 = 0; e0 < E; e0 += kGroup) {
+  for (int e0 = 0; e0 < N; e0 += kGroup) {
     uint64_t acc = 0;
 #pragma unroll
     for (int e = e0; e < e0 + kGroup; ++e) acc += cd[e] < 16 ? 1ull << (4 * cd[e]) : 0ull;
@@ -97,6 +95,11 @@ __device__ __forceinline__ void wave_digit_counts(const int (&cd)[E], uint32_t (
     by[2] += hi & 0x0F0F0F0Fu;
     by[3] += (hi >> 4) & 0x0F0F0F0Fu;
   }
+}
+
+template <int E>
+__device__ __forceinline__ void wave_digit_counts(uint32_t (&by)[4], uint32_t (&cnt)[8]) {
+  static_assert(E <= 128, "byte sums");
   auto row_sum = [](uint32_t x) __attribute__((always_inline)) {  // inclusive: lane 15 holds the row's
     x += dpp32<kDppRowShr1>(x);
     x += dpp32<kDppRowShr2>(x);
@@ -142,10 +145,19 @@ __device__ __forceinline__ void select_topk_regs(const double* __restrict__ scor
     valid[e] = i < m;
     x[e] = order_key(scores[min(i, m - 1)]);  // unconditional load
   }
+  // Past 16 keys, what is kept per key besides the key itself spills (32 keys: flags
+  // in pairs of scalar registers, ballots, digits and indices took 46 registers more
+  // than there are, and 39 us instead of 33): existence is a comparison with the
+  // thread's number of keys, digits are counted eight at a time, and a value passed to
+  // `forget` makes the compiler compute anew what came of it.
+  int n_mine = E > 16 ? (m - tid + THREADS - 1) / THREADS : 0;
+  auto forget = [](auto& value) __attribute__((always_inline)) {
+    if constexpr (E > 16) asm volatile("" : "+v"(value));
+  };
   uint64_t lo = ~0ull, hi = 0;
 #pragma unroll
   for (int e = 0; e < E; ++e)
-    if (valid[e]) {
+    if (E > 16 ? e < n_mine : valid[e]) {
       lo = x[e] < lo ? x[e] : lo;
       hi = x[e] > hi ? x[e] : hi;
     }
@@ -170,14 +182,24 @@ __device__ __forceinline__ void select_topk_regs(const double* __restrict__ scor
     prefix = lo & mask;
     for (;;) {
       // this wave's count of candidates per digit value, digit b in lane b
-      // (cd = 16: not a candidate)
-      int cd[E];
+      // (digit 16: not a candidate)
+      constexpr int kDigits = E > 16 ? 8 : E;
+      uint32_t by[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
-      for (int e = 0; e < E; ++e)
-        cd[e] = valid[e] && (x[e] & mask) == prefix ? (int)((x[e] >> shift) & 15) : 16;
+      for (int e0 = 0; e0 < E; e0 += kDigits) {
+        int cd[kDigits];
+        forget(n_mine);
+#pragma unroll
+        for (int e = 0; e < kDigits; ++e)
+          cd[e] = (E > 16 ? e0 + e < n_mine : valid[e0 + e]) && (x[e0 + e] & mask) == prefix
+                      ? (int)((x[e0 + e] >> shift) & 15)
+                      : 16;
+        add_digits<kDigits>(cd, by);
+        if constexpr (E > 16) __builtin_amdgcn_sched_barrier(0);
+      }
       {
         uint32_t cnt[8];
-        wave_digit_counts<E>(cd, cnt);
+        wave_digit_counts<E>(by, cnt);
         if (lane == 15)
 #pragma unroll
           for (int i = 0; i < 8; ++i) {
@@ -229,8 +251,10 @@ __device__ __forceinline__ void select_topk_regs(const double* __restrict__ scor
     constexpr int kPer = E * kWaves / 64;
 #pragma unroll
     for (int e = 0; e < E; ++e) {
+      if (e % 8 == 0) forget(n_mine);
       const uint64_t xm = x[e] & mask;
-      const uint64_t bg = __ballot(valid[e] && xm > prefix), be = __ballot(valid[e] && xm == prefix);
+      const bool ok = E > 16 ? e < n_mine : valid[e];
+      const uint64_t bg = __ballot(ok && xm > prefix), be = __ballot(ok && xm == prefix);
       if (lane == 0) sh.part[e * kWaves + wave] = __popcll(bg) | ((uint32_t)__popcll(be) << 16);
     }
     __syncthreads();
@@ -255,17 +279,22 @@ __device__ __forceinline__ void select_topk_regs(const double* __restrict__ scor
       }
     }
     __syncthreads();
+    int first = tid;
+    forget(prefix);
+    forget(first);
 #pragma unroll
     for (int e = 0; e < E; ++e) {
+      if (e % 8 == 0) forget(n_mine);
       const uint64_t xm = x[e] & mask;
-      const bool gt = valid[e] && xm > prefix, eq = valid[e] && xm == prefix;
+      const bool ok = E > 16 ? e < n_mine : valid[e];
+      const bool gt = ok && xm > prefix, eq = ok && xm == prefix;
       const uint32_t before = sh.part[e * kWaves + wave];
       const int gt_before = (int)(before & 0xffffu) + __popcll(__ballot(gt) & below);
       const int eq_before = (int)(before >> 16) + __popcll(__ballot(eq) & below);
       if (gt || (eq && eq_before < remaining)) {
         const int pos = gt_before + min(eq_before, remaining);
-        out0[pos] = e * THREADS + tid;
-        if (out1) out1[pos] = e * THREADS + tid;
+        out0[pos] = e * THREADS + first;
+        if (out1) out1[pos] = e * THREADS + first;
       }
     }
     return;
