@@ -106,7 +106,8 @@ __device__ __forceinline__ uint32_t xcd_remap(uint32_t bid, uint32_t nblocks_pad
 // chunks).  The units of every rbh are split into NS segments of floor or ceil
 // of U/NS units: segment s holds units [s*U/NS, (s+1)*U/NS).  One workgroup
 // runs one segment, so the grid is Hkv*RB*NS workgroups of equal work (within
-// one unit); NS is chosen so that the grid fills two workgroups per CU.
+// one unit); NS is chosen so that the grid fills two workgroups per CU, or one where
+// the keys are so few that two would take segments of under four stages.
 struct ScoreWork {
   int32_t rpb;  // rows per row block
   int32_t RB;   // row blocks per KV head
@@ -174,7 +175,6 @@ ckv_status launch_gather(const ckv_dims* d, const void* k_src, const void* v_src
 struct AttnPlan {
   int32_t rows;      // G*S rows per KV head
   int32_t n_splits;  // key splits (1: no combine)
-
   size_t off_o, off_ml, bytes;
 };
 // Keys: the k kept chunks, then (with_suffix) the causal suffix.

@@ -5,10 +5,10 @@
 //
 // Work split.  Rows of one KV head g are r = t*G + i (query t, head g*G+i),
 // grouped in blocks of 256 rows (4 waves x 64).  Each (KV head, row block) pair
-// spans the whole key axis, cut into 256-key items; the items are dealt out in
-// equal contiguous runs to a fixed grid of workgroups, so every workgroup (and
-// CU) does the same work.  The items of one workgroup that share a row block
-// form a segment.  Each wave keeps its 64 query rows in registers as the B
+// spans the whole key axis, cut into units of lcm(64, c) keys; the units are dealt
+// out in runs that differ by at most one (segments), one workgroup each, so every
+// workgroup (and CU) does nearly the same work; a wave past the last rows only helps
+// to stage the keys.  Each wave keeps its 64 query rows in registers as the B
 // operand of bf16 MFMA 32x32x16 and streams the segment's keys through LDS in
 // 64-key stages of two 32-key subtiles, computing S^T = K Q^T so that every
 // lane holds one query row and 16 of the 32 keys of a subtile (its partner lane
@@ -608,8 +608,8 @@ __device__ __forceinline__ void run_segment(const ScoreArgs& a, int g, int64_t k
   }
 }
 
-// Q^T fragments of the wave's 64 rows from my_row0: B operand, lane l holds row l%32 of a row tile
-// and d = 16*ks + 8*half .. +7 (zero past R).
+// Q^T fragments of the wave's 64 rows from my_row0: B operand, lane l holds row l%32
+// of a row tile and d = 16*ks + 8*half .. +7 (zero past R).
 template <int D>
 __device__ __forceinline__ void load_q(const ScoreArgs& a, int g, int my_row0, bf16x8 (&qf)[2][D / 16]) {
   const int lane = threadIdx.x & 63, half = lane >> 5;
@@ -828,59 +828,75 @@ __global__ __launch_bounds__(kWaves * 64, 2) void score_bf16_kernel(ScoreArgs a)
   }
 }
 
+// The flagged segments of row block rbh for the wave's 64 rows from my_row0, by all
+// four waves.
+template <int D, int MODE>
+__device__ __forceinline__ void redo_segments(const ScoreArgs& a, int g, int rbh, int my_row0,
+                                              uint16_t* lds) {
+  for (int s = 0; s < a.w.NS; ++s) {
+    if (!a.flags[rbh * a.w.NS + s]) continue;  // uniform
+    const Segment o = segment_at(a.w, a.n, rbh, s);
+    bf16x8 qf[2][D / 16];
+    load_q<D>(a, g, my_row0, qf);
+    RangeState st;
+    run_segment<D, MODE, 1>(a, g, o.kbeg, o.nkeys, my_row0, qf, lds, st);
+    run_segment<D, MODE, 2>(a, g, o.kbeg, o.nkeys, my_row0, qf, lds, st);
+    store_stats(a, g, s, my_row0, st);
+    __syncthreads();
+  }
+}
+
 // Fold pass, one workgroup per 64 rows of a KV head: redoes exactly (against its
 // own maximum, two passes) any of their segments whose chunk sums left the guard
 // in the main pass -- almost never -- then folds the segments.  In a redo all
 // four waves stage the keys and compute the same 64 rows (and store the same values).
-// OWN (up to kFoldOwn segments): one workgroup per row block, each wave folding 64
-// rows of its own, so that no wave is without a segment and nothing is merged; a wave
-// past the last rows takes part in a redo with those before it.
-template <int D, int MODE, bool OWN>
+template <int D, int MODE>
 __global__ __launch_bounds__(kWaves * 64, 2) void score_fold_kernel(ScoreArgs a) {
   __shared__ __attribute__((aligned(16))) uint16_t lds[2 * kStage * SubtileLds<D>::kRow];
-  const int wave = threadIdx.x >> 6;
-  const int groups = OWN ? a.w.RB : a.w.ldp / kWaveRows;  // per KV head
-  const int g = blockIdx.x / groups;
-  const int row0 = (blockIdx.x % groups) * (OWN ? kBlockRows : kWaveRows) + (OWN ? wave * kWaveRows : 0);
-  const int my_row0 = min(row0, a.w.ldp - kWaveRows);
+  __shared__ FoldLds sh;
+  const int groups = a.w.ldp / kWaveRows;  // per KV head
+  const int g = blockIdx.x / groups, my_row0 = (blockIdx.x % groups) * kWaveRows;
   const int rbh = g * a.w.RB + my_row0 / kBlockRows;
+  const int wave = threadIdx.x >> 6;
   const int64_t base = (int64_t)g * a.w.NS * a.w.ldp + my_row0 + (threadIdx.x & 63);
   // all flags of the block, and (speculatively) the rows' statistics, in one
   // round trip; nothing flagged is the common case
-  constexpr int kB = OWN ? kFoldOwn : kFoldFew, kStride = OWN ? 1 : kWaves;
-  const int s0 = OWN ? 0 : wave;
-  const bool few = a.w.NS <= kB * kStride;
-  FoldRegs<kB> r;
-  if (few) fold_load<kB, kStride>(a.mc, a.z, a.w, base, s0, r);
+  const bool few = a.w.NS <= kFoldFew * kWaves;
+  FoldRegs<kFoldFew> r;
+  if (few) fold_load<kFoldFew>(a.mc, a.z, a.w, base, wave, r);
   int any = 0;
   for (int s = threadIdx.x; s < a.w.NS; s += blockDim.x) any |= a.flags[rbh * a.w.NS + s];
   const bool redo = __syncthreads_or(any);
+  if (redo) redo_segments<D, MODE>(a, g, rbh, my_row0, lds);
+  if (!few) {
+    fold_rows_batched<kFoldMany>(a.mc, a.z, a.w, base, sh);
+    return;
+  }
+  if (redo) fold_load<kFoldFew>(a.mc, a.z, a.w, base, wave, r);  // the rows as redone
+  fold_rows<kFoldFew>(a.z, a.w, base, sh, r);
+}
+
+// The same for up to kFoldOwn segments: one workgroup per row block, each wave folding
+// 64 rows of its own, so that no wave is without a segment and nothing is merged.  A
+// wave past the last rows takes part in a redo with those before it.
+template <int D, int MODE>
+__global__ __launch_bounds__(kWaves * 64, 2) void score_fold_own_kernel(ScoreArgs a) {
+  __shared__ __attribute__((aligned(16))) uint16_t lds[2 * kStage * SubtileLds<D>::kRow];
+  const int g = blockIdx.x / a.w.RB, rbh = blockIdx.x;
+  const int row0 = (rbh % a.w.RB) * kBlockRows + (int)(threadIdx.x >> 6) * kWaveRows;
+  const int my_row0 = min(row0, a.w.ldp - kWaveRows);
+  const int64_t base = (int64_t)g * a.w.NS * a.w.ldp + my_row0 + (threadIdx.x & 63);
+  FoldRegs<kFoldOwn> r;
+  fold_load<kFoldOwn, 1>(a.mc, a.z, a.w, base, 0, r);
+  const bool redo = __syncthreads_or((int)threadIdx.x < a.w.NS ? a.flags[rbh * a.w.NS + threadIdx.x] : 0);
   if (redo) {
-    for (int s = 0; s < a.w.NS; ++s) {
-      if (!a.flags[rbh * a.w.NS + s]) continue;  // uniform
-      const Segment o = segment_at(a.w, a.n, rbh, s);
-      bf16x8 qf[2][D / 16];
-      load_q<D>(a, g, my_row0, qf);
-      RangeState st;
-      run_segment<D, MODE, 1>(a, g, o.kbeg, o.nkeys, my_row0, qf, lds, st);
-      run_segment<D, MODE, 2>(a, g, o.kbeg, o.nkeys, my_row0, qf, lds, st);
-      store_stats(a, g, s, my_row0, st);
-      __syncthreads();
-    }
-    if (few) fold_load<kB, kStride>(a.mc, a.z, a.w, base, s0, r);  // the rows as redone
+    redo_segments<D, MODE>(a, g, rbh, my_row0, lds);
+    fold_load<kFoldOwn, 1>(a.mc, a.z, a.w, base, 0, r);  // the rows as redone
   }
-  if constexpr (OWN) {
-    float M;
-    double Z;
-    fold_sum<kB>(r, M, Z);
-    if (row0 < a.w.ldp) fold_store<kB, 1>(a.z, a.w, base, 0, r, M, 1.0 / Z);
-  } else {
-    __shared__ FoldLds sh;
-    if (few)
-      fold_rows<kB>(a.z, a.w, base, sh, r);
-    else
-      fold_rows_batched<kFoldMany>(a.mc, a.z, a.w, base, sh);
-  }
+  float M;
+  double Z;
+  fold_sum<kFoldOwn>(r, M, Z);
+  if (row0 < a.w.ldp) fold_store<kFoldOwn, 1>(a.z, a.w, base, 0, r, M, 1.0 / Z);
 }
 
 // fp32 path: the main kernel already redid overflowing segments; fold only.
@@ -1344,9 +1360,9 @@ ckv_status launch_score(const ckv_dims* d, const void* q, const void* k, double*
     hipLaunchKernelGGL((score_bf16_kernel<DD, MM>), grid, block, 0, st, a);                \
     if (main_stop) CKV_HIP(hipEventRecord(main_stop, st));                                \
     if (own)                                                                               \
-      hipLaunchKernelGGL((score_fold_kernel<DD, MM, true>), fold_grid, block, 0, st, a);   \
+      hipLaunchKernelGGL((score_fold_own_kernel<DD, MM>), fold_grid, block, 0, st, a);     \
     else                                                                                   \
-      hipLaunchKernelGGL((score_fold_kernel<DD, MM, false>), fold_grid, block, 0, st, a);  \
+      hipLaunchKernelGGL((score_fold_kernel<DD, MM>), fold_grid, block, 0, st, a);         \
   } while (0)
     if (d->head_dim == 128) {
       switch (mode) {

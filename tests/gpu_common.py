@@ -93,8 +93,8 @@ SCORE_RTOL_BOUND = 2e-6
 #   u |o|   the output's rounding to bf16;
 #   u a     the numerators rounded to bf16 for the P V product (the
 #           denominator sums them unrounded);
-#   u a     each split's normalised partial stored in bf16 (the combine
-#           weights sum to one);
+#   u a     each split's partial, for bf16 (the combine weights sum to one; half
+#           precision with an exponent per row, as stored, takes u a / 8);
 # plus the fp32 effects -- logits accumulated over head_dim, O over a split's
 # keys, the denominators and combine weights -- which stay below 2^-11 a.
 # Each element is held to the smaller of that bound and the stated max-abs
