@@ -38,11 +38,12 @@
 // maximum, register staging and operands read right before their MFMA, at 1.85
 // GHz (what the chip holds under this load): 32K layer 27 -> 24 us, 64K layer
 // 154 -> 119 us, 128K layer 367 -> 286 us, 8,000 of 16,000 tokens with 512
-// queries and 32 heads 107 -> 72 us (949 TFLOP/s).  Not faster: 64 rows per wave
-// (half the LDS reads, one wave per SIMD: 3,350 cycles per stage and 64 rows,
-// two waves of 32 rows 3,440), and a loop that spreads the numerators over all
-// 32 MFMAs by running a product of the next stage early (128K 295 against 302 us
-// of the loop below, small grids 10% slower for its longer prologue).
+// queries and 32 heads, with their combine, 103 -> 75 us (920 TFLOP/s).  Not
+// faster: 64 rows per wave (half the LDS reads, one wave per SIMD: 3,350 cycles per
+// stage and 64 rows, two waves of 32 rows 3,440), and a loop that spreads the
+// numerators over all 32 MFMAs by running a product of the next stage early (128K
+// 295 against 302 us of the loop below, small grids 10% slower for its longer
+// prologue).
 //
 // A slice that is done again costs its workgroup a pass over its K rows and a second
 // pass of everything.  With every slice done again (in each 64 keys one 90 log2
