@@ -992,8 +992,10 @@ AttnPlan make_attn_plan(const ckv_dims* d, int64_t k, bool with_suffix) {
   const int64_t n_max = attn_most_splits(d, ntiles);
   int64_t splits = 0;
   double best = 0;
-  int64_t per = 0;  // stages per split: each candidate once
-  for (int64_t n0 = n_min; n0 <= n_max; n0 = per > 1 ? ceil_div(ntiles, per - 1) : n_max + 1) {
+  // (past sqrt(ntiles) many counts give the same stages per split: on to the next that
+  // does not; below, the divisions of a count do not wait for those of the last)
+  for (int64_t n0 = n_min, per = 0; n0 <= n_max;
+       n0 = n0 * n0 < ntiles || per == 1 ? n0 + 1 : ceil_div(ntiles, per - 1)) {
     per = ceil_div(ntiles, n0);
     const int64_t n = ceil_div(ntiles, per), wgs = base * n, rem = wgs % 512;
     double cost = (double)(wgs / 512) * (kFixed + kStage * (double)per);
