@@ -46,11 +46,11 @@
 // prologue).
 //
 // A slice that is done again costs its workgroup a pass over its K rows and a second
-// pass of everything.  With every slice done again (in each 64 keys one 90 log2
-// units above the others): 32K layer 31 -> 49 us, 64K 111 -> 267, 8K 11.5 -> 19.4,
-// 8,000 tokens x 32 heads 77 -> 176; a running maximum took 32, 143, 12.1 and 103 us
-// on these inputs.  It takes a logit 64 log2 units (44 nats) above all of the slice's
-// first keys.
+// pass of everything.  With every slice done again (in each 64 keys one 130 log2
+// units above the others): 32K layer 31 -> 48 us, 64K 113 -> 262, 8K 11.5 -> 19.2,
+// 8,000 tokens x 32 heads 79 -> 173; a running maximum took 32, 139, 12.0 and 100 us
+// on these inputs.  It takes a logit 120 log2 units (83 nats) above all of the slice's
+// first keys, or outputs past fp32; up to there a low reference costs nothing.
 
 #include <atomic>
 #include <type_traits>
@@ -68,7 +68,9 @@ constexpr int kWaveRows = 32;
 constexpr int kBlockRows = kWaves * kWaveRows;  // 128
 constexpr int kTile = 64;                       // keys per LDS stage
 constexpr int kSub = 32;                        // keys per MFMA product
-constexpr float kGuard = 0x1p64f;               // a sum of numerators above this is taken again
+// A slice is done again when its sum of numerators passes kGuard (1 / sum stays a normal
+// number below it), or lies below kGuardLow without a reference.
+constexpr float kGuard = 0x1p120f, kGuardLow = 0x1p-64f;
 // Unit tables: a slice's keys in units of min(c, 32) keys, each inside one chunk
 // or inside the suffix (kc is a multiple of c).  base: the unit's first row in
 // its source (a byte offset when every row of both sources lies below 4 GiB);
@@ -633,7 +635,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attn_kernel(AttnArgs a) {
     const uint32_t total = __float_as_uint((any[0] + any[1]) + (any[2] + any[3]));
     const bool bad = (total & 0x7f800000u) == 0x7f800000u ||
                      (__float_as_uint(l[0]) & 0x7fffffffu) > __float_as_uint(kGuard) ||
-                     (no_ref && l[0] < 1.f / kGuard && sees_key());
+                     (no_ref && l[0] < kGuardLow && sees_key());
     if (!__syncthreads_or(bad)) break;
     float mx = -INFINITY;
     for (int st = 0; st < nt; ++st) {
